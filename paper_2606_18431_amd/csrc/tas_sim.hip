@@ -108,6 +108,10 @@ DEV uint64_t rlu(uint64_t x, int l) {
 }
 DEV int64_t rl64(int64_t x, int l) { return (int64_t)rlu((uint64_t)x, l); }
 DEV uint64_t uniu(uint64_t x) { return rlu(x, __builtin_amdgcn_readfirstlane(lane())); }
+DEV uint64_t sgpr64(uint64_t x) {
+    const uint32_t lo = (uint32_t)uni((int)(uint32_t)x), hi = (uint32_t)uni((int)(uint32_t)(x >> 32));
+    return ((uint64_t)hi << 32) | lo;
+}
 // One wavefront is the whole workgroup and its LDS operations execute in
 // issue order, so ordering LDS traffic between lanes only needs the compiler
 // not to move memory operations across this point.
@@ -312,9 +316,10 @@ struct Sim {
     int64_t pa;
     int pP, pD;
     int64_t iters, reqiters, tokens, ev_vol, ev_forced, maxU, idle;
-    // loop steps for the launch-order key: formation passes and emission
-    // chunks (32-bit: a wrap only perturbs the order of a huge instance)
-    uint32_t fpass, echunks;
+    // loop steps for the launch-order key: steps (an iteration, or a run of
+    // repeated ones), formation passes and emission chunks (32-bit: a wrap
+    // only perturbs the order of a huge instance)
+    uint32_t steps, fpass, echunks;
     // CL: the replica (wave) index, the global indices dispatched to it in
     // order (HBM, written and read by this wave only, through L2), how many,
     // the prefetched global index of each lane, and the completions of the
@@ -327,12 +332,10 @@ struct Sim {
     uint64_t emit_chunks;  // 64-entry chunks holding batch members or evictions
     bool emit_all;         // ranks moved during formation: visit every chunk
     // Repeated batch: the next iteration's formation would select every
-    // resident with one token each and nothing else (see run), so it is
-    // skipped. Emission reports whether every batch member emitted a token
-    // and how many new KV blocks the members need for their next token.
+    // resident with one token each and nothing else (see step), so it is
+    // skipped. Emission reports whether every batch member emitted a token.
     bool rep, all_emit;
-    int du_next;
-    int nmoved;  // entries whose key the latest emission moved
+    int nmoved;  // entries whose key the latest emission or streak moved
     // the key of the waiting candidate that closed admissions in the latest
     // formation (~0: none), the smallest key of the arrivals taken since
     // (~0: none) and a count of spill_excess calls
@@ -410,19 +413,40 @@ struct Sim {
         lo_hole = INT32_MAX;
         spill_min = ~0ull;
         iters = reqiters = tokens = ev_vol = ev_forced = maxU = idle = 0;
-        fpass = echunks = 0;
+        steps = fpass = echunks = 0;
         cnt = used = 0;
         sum_ctx = 0;
         emit_chunks = 0;
         emit_all = false;
         rep = all_emit = false;
-        du_next = 0;
         nmoved = 0;
         close_pk = arr_min_pk = ~0ull;
         n_spilled = 0;
         vm_res = vm_ev = 0;
         vm_ok = false;
         wsync();
+    }
+
+    // The wave-uniform state back in scalar registers: 64-bit comparisons and
+    // selects have no scalar form here, and values that pass through one
+    // would otherwise live in vector registers around the whole loop.
+    DEV void pin() {
+        t = (int64_t)sgpr64((uint64_t)t);
+        sum_ctx = (int64_t)sgpr64((uint64_t)sum_ctx);
+        iters = (int64_t)sgpr64((uint64_t)iters);
+        reqiters = (int64_t)sgpr64((uint64_t)reqiters);
+        tokens = (int64_t)sgpr64((uint64_t)tokens);
+        ev_vol = (int64_t)sgpr64((uint64_t)ev_vol);
+        ev_forced = (int64_t)sgpr64((uint64_t)ev_forced);
+        maxU = (int64_t)sgpr64((uint64_t)maxU);
+        idle = (int64_t)sgpr64((uint64_t)idle);
+        spill_min = sgpr64(spill_min);
+        close_pk = sgpr64(close_pk);
+        arr_min_pk = sgpr64(arr_min_pk);
+        emit_chunks = sgpr64(emit_chunks);
+        U = uni(U), L = uni(L), nW = uni(nW), nR = uni(nR), n_holes = uni(n_holes);
+        lo_hole = uni(lo_hole), spill_n = uni(spill_n), next = uni(next), pf = uni(pf);
+        completed = uni(completed), status = uni(status), n_spilled = uni(n_spilled);
     }
 
     DEV void fail(int code) {
@@ -572,8 +596,7 @@ struct Sim {
             if (LIKELY(n_arr == 0)) return;
             const R x = new_record(CL ? pidx : r, pa, pP, pD);
             const R y = off ? shfl_rec(x, min(off + lane(), kWave - 1)) : x;
-            if constexpr (!CL && !EXT)
-                arr_min_pk = min(arr_min_pk, wminu(lane() < n_arr ? y.pk : ~0ull));
+            arr_min_pk = min(arr_min_pk, wminu(lane() < n_arr ? y.pk : ~0ull));
             nW += n_arr;
             next += n_arr;
             add_entries(y, n_arr);
@@ -1106,16 +1129,12 @@ struct Sim {
 
     // ---------------------------------------------------------- execute
 
-    // Returns the lowest rank whose key moved (INT32_MAX if none). Batch
-    // members are the entries whose flags meet `mem` (G_INB; in a repeated
-    // batch also G_RES), with `n1` added to their scheduled tokens (1 in a
-    // repeated batch, whose entries carry no token count).
-    DEV int emission(int64_t t_end, uint32_t mem, int n1) {
-        int lo = INT32_MAX, lohole = INT32_MAX, nd = 0, ufree = 0, nmv = 0;
+    // Returns the lowest rank whose key moved (INT32_MAX if none).
+    DEV int emission(int64_t t_end) {
+        int lo = INT32_MAX, lohole = INT32_MAX, nd = 0, ufree = 0, kfree = 0, nmv = 0;
         nmoved = 0;
         bool bad_idx = false;
         uint64_t noemit = 0;  // batch members that emitted no token
-        int dnext = 0;        // members whose next token opens a KV block
         const uint32_t t32 = (uint32_t)t_end;
         const int nch = (L + kWave - 1) >> 6;
         // LTR+ updates every candidate's starvation count: visit every chunk
@@ -1149,13 +1168,12 @@ struct Sim {
             const uint32_t g = r < L ? q.x : 0u;
             // Per lane, as selects: the flag tests below are lane-dependent,
             // and a branch on them would cost scalar exec-mask work in every
-            // chunk. Members (flags meet `mem`) advance; entries evicted in
+            // chunk. Members advance; entries evicted in
             // this iteration lose the eviction mark.
-            const bool memb = (g & mem) != 0;
+            const bool memb = (g & G_INB) != 0;
             const bool evi = !memb && (g & G_EVI) != 0;
             int w = sw(q), left = sleft(q);
-            const int kv0 = skv(q);
-            int kv = kv0 + n1;  // includes this iteration's chunk (added at admission)
+            int kv = skv(q);  // includes this iteration's chunk (added at admission)
             const int idx = idx_of(pk);
             bad_idx = bad_idx || (memb && idx >= N);
             const bool emit = memb && kv == w && idx < N;
@@ -1170,12 +1188,13 @@ struct Sim {
             uint32_t gs = (memb ? g & ~G_INB : g & ~G_EVI) | (first ? G_FIRST : 0u);
             gs = fin ? (gs | G_DONE) & ~G_RES : gs;
             ufree += fin ? blocks(kv) : 0;
+            kfree += fin ? kv : 0;
             if (first) tfirst[idx] = t_end;
             if (fin) {
                 tlast[idx] = t_end;
                 tbo[idx] = gm;
             }
-            kv = fin ? 0 : (memb ? kv : kv0);
+            kv = fin ? 0 : kv;
             const bool live = emit && !fin;  // emitted and has tokens left
             bool chg = false;
             uint64_t pk2 = pk;
@@ -1229,7 +1248,6 @@ struct Sim {
             const bool dirty = chg && pol != P_SRPT && pol != P_TRAIL;
             gs |= dirty ? G_DIRTY : 0u;
             const bool mute = memb && !emit;
-            const bool opens = live && blocks(kv + 1) != blocks(kv);
             if (memb || evi) {
                 stq(r, gs, w, kv, left);
                 S.k[r] = pk2;
@@ -1253,7 +1271,6 @@ struct Sim {
             }
             const uint64_t cm = ballot(chg), fm = ballot(fin);
             noemit |= ballot(mute);
-            dnext += popc(ballot(opens));
             if (cm) {
                 nmv += popc(cm);
                 if (lo == INT32_MAX) lo = b + ffs0(cm);
@@ -1281,15 +1298,252 @@ struct Sim {
         if (ballot(bad_idx)) fail(S_ESTATE);
         all_emit = noemit == 0;
         nmoved = nmv;
-        du_next = dnext;
         if (nd) {
             U -= wsum(ufree);
+            sum_ctx -= wsum(kfree);
             completed += nd;
             nR -= nd;
             n_holes += nd;
             lo_hole = min(lo_hole, lohole);
         }
         return lo;
+    }
+
+    // A run of repeated iterations (rep): the members are all the residents,
+    // each takes one token per iteration, and nothing else changes until the
+    // first event - a completion, a key that moves otherwise than with all
+    // the others (a level crossing, an LTR+ promotion or demotion), an
+    // arrival, a KV budget that the next blocks would exceed, `limit`
+    // (CL), a new grid cell (adaptive gamma) or the iteration limit. The
+    // outcome of r such iterations has a closed form per member, so they are
+    // applied in one pass instead of r. The iterations' costs differ only in
+    // the context sum, which grows by the members each time: lane j computes
+    // the j-th cost and a prefix sum their end times, so the run is at most
+    // 64 long. The events of the r-th iteration itself are applied too.
+    // Returns r (0: the next iteration needs a formation; nothing was done)
+    // and sets `lo` to the lowest rank that must be re-inserted.
+    //
+    // What bounds an instance is its own chain of iterations (about 10,000
+    // cycles each for one formation and emission, on an idle or a full chip
+    // alike), so fewer steps are worth more than cheaper ones: 64 to 97 % of
+    // the iterations of the sweeps below the KV limit repeat the batch before
+    // them, 5 to 25 in a row. Eight instances of 1,000 requests went from
+    // 147 ms to 11.4 ms, 16,384 instances of 8,000 from 1,181 to 658 ms.
+    DEV int streak(int64_t limit, int &lo) {
+        lo = INT32_MAX;
+        nmoved = 0;
+        // time: the r-th iteration starts before the next arrival and `limit`
+        int64_t stop = limit;
+        if (next < n_known()) {
+            int off = next - pf;
+            if (off >= kWave) {
+                pf = next;
+                load_pf();
+                off = 0;
+            }
+            const int64_t an = rl64(pa, off);
+            stop = an < stop ? an : stop;
+        }
+        const int64_t fixed = (int64_t)base + (int64_t)tok * nR;
+        const int64_t top = sum_ctx + (int64_t)kWave * nR;  // the context of iteration 64
+        if (UNLIKELY(fixed >= (1 << 24) || (top >> 32))) return 0;
+        const uint64_t qt = ctx_quot((uint64_t)(sum_ctx + (int64_t)(lane() + 1) * nR));
+        if (UNLIKELY((uint32_t)rl((int)(uint32_t)qt, 63) >= (1u << 24))) return 0;
+        const int cost = (int)fixed + (int)qt;
+        const int tend = scan_add(cost);  // below 64 * 2^25
+        const int64_t room = stop - t;    // > 0
+        int r = kWave;
+        if (room <= INT32_MAX) {
+            const uint64_t late = ballot(tend >= (int)room);
+            if (late) r = ffs0(late) + 1;
+        }
+        if (max_iters - iters < r) r = (int)(max_iters - iters);
+        // events of the members (and, under LTR+, of the waiting entries)
+        const int nch = (L + kWave - 1) >> 6;
+        const bool all = EXT && pol == P_LTR;
+        const uint64_t chunks = all ? (nch >= 64 ? ~0ull : ((1ull << nch) - 1ull)) : emit_chunks;
+        int ev = r;
+        for (uint64_t todo = chunks; todo; todo &= todo - 1) {
+            const int i = ffs0(todo) * kWave + lane();
+            const uint4 q = ldq(min(i, L - 1));
+            const uint32_t g = i < L ? q.x : 0u;
+            const bool res = (g & G_RES) != 0;
+            int e = sleft(q);
+            if (pol == P_BOOST) {  // tokens to the next level's threshold k 2^(level+1)
+                const int up = (int)((g >> G_LVL_SHIFT) & 31u) + 1;
+                int sig = sw(q);
+                if constexpr (EXT) {
+                    if (phase_signal || cache_signal) {
+                        const int ix = min(idx_of(S.k[min(i, L - 1)]), N - 1);
+                        sig -= phase_signal ? Pp[ix] : Hp[ix];
+                    }
+                }
+                // (signals stay below 2^24: a threshold beyond is never reached)
+                if (k <= (0xffffff >> up)) e = min(e, (k << up) - sig);
+            }
+            if constexpr (EXT) {
+                if (pol == P_LTR && (g & G_PROMO)) e = min(e, max((int)(g >> kLtrShift), 1));
+                if (pol == P_LTR && i < L && !(g & (G_RES | G_DONE | G_PROMO)))
+                    ev = min(ev, ltr_s - (int)(g >> kLtrShift));
+            }
+            if (res) ev = min(ev, e);
+        }
+        r = wmin(ev);
+        if (r <= 0) return 0;
+        // KV: every iteration's new blocks fit (the growth only adds up, so the
+        // last one's total decides); halved until they do
+        while (UNLIKELY(U + (int64_t)nR * blocks(r) > Kb)) {
+            int grow = 0;
+            for (uint64_t todo = emit_chunks; todo; todo &= todo - 1) {
+                const int i = ffs0(todo) * kWave + lane();
+                const uint4 q = ldq(min(i, L - 1));
+                const int kv = skv(q);
+                if (i < L && (q.x & G_RES)) grow += blocks(kv + r) - blocks(kv);
+            }
+            if ((int64_t)U + wsum(grow) <= Kb) break;
+            r >>= 1;
+            if (r == 0) return 0;
+        }
+        if constexpr (EXT) {
+            if (ad) {
+                r = ada_hold(r);
+                if (r == 0) return 0;
+            }
+        }
+        // apply r iterations
+        const int64_t t_end = t + rl(tend, r - 1);
+        const uint32_t t32 = (uint32_t)t_end, gap = (uint32_t)rl(cost, r - 1);  // costs never shrink
+        int lohole = INT32_MAX, nd = 0, grow = 0, ufree = 0, kfree = 0;
+        steps++;
+        echunks += popc(chunks);
+        for (uint64_t todo = chunks; todo; todo &= todo - 1) {
+            const int b = ffs0(todo) * kWave;
+            const int i = b + lane(), i0 = min(i, L - 1);
+            const uint4 q = ldq(i0);
+            const uint2 tg = S.tg[i0];
+            const uint32_t g = i < L ? q.x : 0u;
+            const bool memb = (g & G_RES) != 0;
+            const int w = sw(q) + r, left = sleft(q) - r;
+            int kv = skv(q);
+            grow += memb ? blocks(kv + r) - blocks(kv) : 0;
+            kv += r;
+            const bool fin = memb && left == 0;
+            ufree += fin ? blocks(kv) : 0;
+            kfree += fin ? kv : 0;
+            uint32_t gs = fin ? (g | G_DONE) & ~G_RES : g;
+            const uint32_t gm = gap > tg.y ? gap : tg.y;
+            const uint64_t fm = ballot(fin);
+            if (fm) {
+                const int idx = idx_of(S.k[i0]);
+                if (fin) {
+                    tlast[idx] = t_end;
+                    tbo[idx] = gm;
+                }
+                if (lohole == INT32_MAX) lohole = b + ffs0(fm);
+                nd += popc(fm);
+                if (vm_ok && lane() == (b >> 6)) vm_res &= ~fm, vm_ev &= ~fm;
+                if constexpr (EXT) {
+                    if (ad) {
+                        uint32_t lat = 0;
+                        if (fin) {
+                            const int64_t e2e = t_end - arr[idx];
+                            lat = e2e > 0xFFFFFFFFll ? 0xFFFFFFFFu : (uint32_t)e2e;
+                        }
+                        for (uint64_t m = fm; m; m &= m - 1)
+                            ada_push((uint32_t)rl((int)lat, ffs0(m)));
+                    }
+                }
+            }
+            uint64_t cm = 0;  // entries to re-insert
+            if (pol == P_BOOST) {
+                const int ol = (int)((g >> G_LVL_SHIFT) & 31u);
+                int sig = w;
+                if constexpr (EXT) {
+                    if (phase_signal || cache_signal) {
+                        const int ix = min(idx_of(S.k[i0]), N - 1);
+                        sig -= phase_signal ? Pp[ix] : Hp[ix];
+                    }
+                }
+                const bool chg = memb && !fin && k <= (0xffffff >> (ol + 1)) &&
+                                 sig >= (k << (ol + 1));
+                cm = ballot(chg);
+                if (cm) {
+                    const uint64_t pk = S.k[i0];
+                    if (chg) {
+                        const int nl = level_of(sig, k, lk);
+                        S.k[i] = pack(key_of(pk) + S.bt[ol] - S.bt[nl], idx_of(pk));
+                        gs = (gs & ~G_LVL) | ((uint32_t)nl << G_LVL_SHIFT) | G_DIRTY;
+                    }
+                }
+            } else if (pol == P_SRPT || pol == P_TRAIL || pol == P_LAS) {
+                // every member's key moves by r; holes move along, so that the
+                // residents and holes stay in order
+                const uint64_t d = (uint64_t)(uint32_t)r << kIdxBits;
+                const uint64_t pk = S.k[i0];
+                if (memb || (g & G_DONE)) S.k[i] = pol == P_LAS ? pk + d : pk - d;
+                // past a waiting entry, perhaps: compaction finds those
+                if (pol != P_LAS && nW > 0) cm = ballot(memb && !fin);
+            }
+            if constexpr (EXT) {
+                if (pol == P_SARATHI) {  // all to the same, latest key: they stay in order
+                    const int idx = idx_of(S.k[i0]);
+                    if (memb && !fin) S.k[i] = pack(t_end - kDecodeQueueOff, idx);
+                } else if (pol == P_LTR) {
+                    bool chg = false;
+                    const uint64_t pk = S.k[i0];
+                    if (memb && !fin) {
+                        const int quota = (int)(g >> kLtrShift);
+                        if (!(g & G_PROMO)) {
+                            gs &= G_FLAGS;
+                        } else if (quota <= r) {  // the quantum ends: back to key D
+                            gs = (gs & G_FLAGS & ~G_PROMO) | G_DIRTY;
+                            const int idx = idx_of(pk);
+                            S.k[i] = pack((int64_t)(w - Pp[idx]) + left, idx);
+                            chg = true;
+                        } else {
+                            gs -= (uint32_t)r << kLtrShift;
+                        }
+                    } else if (i < L && !(g & (G_RES | G_DONE | G_PROMO))) {
+                        const uint32_t c2 = (g >> kLtrShift) + (uint32_t)r;
+                        uint32_t gx = (g & G_FLAGS) | (c2 << kLtrShift);
+                        if ((int)c2 >= ltr_s) {  // promoted at the end of the r-th iteration
+                            gx = (g & G_FLAGS) | G_PROMO | G_DIRTY |
+                                 ((uint32_t)ltr_q << kLtrShift);
+                            S.k[i] = pack(iters + r - kPromotedOff, idx_of(pk));
+                            chg = true;
+                        }
+                        stx(i, gx);
+                    }
+                    cm = ballot(chg);
+                }
+            }
+            if (memb) {
+                stq(i, gs, w, fin ? 0 : kv, left);
+                S.tg[i] = make_uint2(t32, gm);
+            }
+            if (cm) {
+                nmoved += popc(cm);
+                if (lo == INT32_MAX) lo = b + ffs0(cm);
+            }
+        }
+        wsync();
+        if (pol == P_TRAIL) vm_ok = false;  // eligibility depends on progress
+        iters += r;
+        reqiters += (int64_t)r * nR;
+        tokens += (int64_t)r * nR;
+        sum_ctx += (int64_t)r * nR;
+        U += wsum(grow);
+        if (U > maxU) maxU = U;
+        if (nd) {
+            U -= wsum(ufree);
+            sum_ctx -= wsum(kfree);
+            completed += nd;
+            nR -= nd;
+            n_holes += nd;
+            lo_hole = min(lo_hole, lohole);
+        }
+        t = t_end;
+        return r;
     }
 
     // From rank `from` on: remove holes; extract entries whose key moved
@@ -1444,7 +1698,9 @@ struct Sim {
         emit_chunks = m;
     }
 
-    DEV void maintenance(int lo_mod) {
+    // Returns whether entries may have moved to other ranks.
+    DEV bool maintenance(int lo_mod) {
+        bool edited = false;
         if constexpr (EXT) {
             // Sarathi moves every decode that emitted to the same, latest key:
             // when all decodes were in the batch (steady decoding) the list
@@ -1457,9 +1713,11 @@ struct Sim {
             (ldx(lo_mod) & G_RES)) {
             move_one(lo_mod);  // one resident re-keyed (a level crossing, say)
             lo_mod = L;
+            edited = true;
         }
         if (UNLIKELY(lo_mod < L || n_holes >= kHoleLimit || L > cap_now())) {
             R stage;
+            edited = true;
             const int nx = compact_extract(min(min(lo_mod, lo_hole), L), stage);
             if (nx > kStage) hbm_fence();
             if (L > cap_now()) spill_excess();  // a refill during formation used the overflow region
@@ -1474,6 +1732,7 @@ struct Sim {
             }
         }
         if (status == 0) take_arrivals();
+        return edited;
     }
 
     // ---------------------------------------------------------- adaptive gamma
@@ -1529,6 +1788,51 @@ struct Sim {
         wsync();
     }
 
+    // gamma_hat for the window of wn >= min_samples latencies (the stored
+    // estimate while the window has not changed).
+    DEV double ada_ghat(int wn) const {
+#pragma clang fp contract(off)
+        const AdaLds &G = *S.as;
+        if (!uni(G.wnew)) return G.ghat;
+        const int r95 = (95 * wn + 99) / 100, r99 = (99 * wn + 99) / 100;
+        const uint32_t t95 = S.ws[r95 - 1], t99 = S.ws[r99 - 1];
+        double d = (double)(t99 - t95);
+        if (d < ad->eps) d = ad->eps;
+        return ad->num / d;
+    }
+
+    // UpdateGamma over up to r iterations in which no request completes:
+    // every update is the one ada_update makes, until one would move to
+    // another grid cell. Returns how many stay in the cell (at most r) and
+    // stores the state after them.
+    DEV int ada_hold(int r) {
+#pragma clang fp contract(off)
+        AdaLds &G = *S.as;
+        const int wn = uni(G.wn);
+        if (wn < uni(G.min_samples)) return r;
+        const double gh = ada_ghat(wn);
+        const int cell = uni(G.cell);
+        const double keep = 1.0 - ad->beta, pull = ad->beta * gh;
+        const double gmin = ad->gmin, gmax = ad->gmax;
+        double g = G.gamma;
+        int j = 0;
+        for (; j < r; j++) {
+            double x = keep * g + pull;
+            if (x < gmin) x = gmin;
+            if (x > gmax) x = gmax;
+            if (popc(ballot(x >= bnd)) != cell) break;
+            if (!ballot(x != g)) {  // a fixed point: every later update gives it again
+                j = r;
+                break;
+            }
+            g = x;
+        }
+        wsync();
+        if (j > 0 && lane() == 0) G.gamma = g, G.ghat = gh, G.wnew = 0;
+        wsync();
+        return j;
+    }
+
     // UpdateGamma (Phase 4, Algorithm 2), before the keys of every iteration:
     // with at least min_samples latencies in the window, gamma_hat =
     // tau ln 5 / max(t99 - t95, eps) from the nearest-rank t95, t99 (only
@@ -1540,14 +1844,7 @@ struct Sim {
         AdaLds &G = *S.as;
         const int wn = uni(G.wn);
         if (wn < uni(G.min_samples)) return;
-        double gh = G.ghat;
-        if (uni(G.wnew)) {
-            const int r95 = (95 * wn + 99) / 100, r99 = (99 * wn + 99) / 100;
-            const uint32_t t95 = S.ws[r95 - 1], t99 = S.ws[r99 - 1];
-            double d = (double)(t99 - t95);
-            if (d < ad->eps) d = ad->eps;
-            gh = ad->num / d;
-        }
+        const double gh = ada_ghat(wn);
         double g = (1.0 - ad->beta) * G.gamma + ad->beta * gh;
         if (g < ad->gmin) g = ad->gmin;
         if (g > ad->gmax) g = ad->gmax;
@@ -1687,6 +1984,108 @@ struct Sim {
 
     // ---------------------------------------------------------- driver
 
+    // Nothing arrived since `next0`, or all that arrived is met after the
+    // waiting candidate that closed admissions, and so skipped, and nothing
+    // was spilled to make room (the on-chip list keeps every waiting entry it
+    // had): the arrivals do not change a repeated batch.
+    DEV bool arrivals_keep(int next0, int sp0) const {
+        return n_spilled == sp0 &&
+               (next == next0 || (close_pk != ~0ull && arr_min_pk > close_pk));
+    }
+
+    // Sarathi: the first live entry of the list is a resident, so no waiting
+    // request that emitted tokens (whose older decode-queue key ranks ahead
+    // of every resident served just now) is met before them.
+    DEV bool resident_first() const {
+        for (int b = 0; b < L; b += kWave) {
+            const int i = b + lane();
+            const uint32_t g = i < L ? ldx(i) : G_DONE;
+            const uint64_t live = ballot(!(g & G_DONE)), res = ballot((g & G_RES) != 0);
+            if (live) return (res >> ffs0(live)) & 1ull;
+        }
+        return false;
+    }
+
+    // One iteration, or a run of repeated ones; then the list's maintenance
+    // and the arrivals. `limit`: see streak.
+    DEV void step(int64_t limit) {
+        pin();
+        const int c0 = completed, next0 = next, sp0 = n_spilled;
+        int lo_mod = INT32_MAX;
+        // whole: the batch held every resident and each emitted a token, so
+        // each needs exactly one next; stays: see below
+        bool whole = true, stays = true;
+        if (!(rep && streak(limit, lo_mod) > 0)) {
+            if constexpr (EXT) {
+                if (ad) {
+                    ada_update();
+                    if (status) return;
+                }
+            }
+            const int64_t ev0 = ev_vol + ev_forced;
+            formation();
+            if (status) return;
+            if (cnt == 0) {
+                fail(S_ESTATE);
+                return;
+            }
+            if constexpr (kCheck) {
+                check_batch();
+                if (status) return;
+            }
+            whole = cnt == nR;
+            // formation evicted nothing, refilled nothing and stopped short
+            // of the token budget
+            stays = ev_vol + ev_forced == ev0 && !emit_all && used < T;
+            if (U > maxU) maxU = U;
+            const int64_t dt =
+                (int64_t)base + (int64_t)tok * used + (int64_t)ctx_quot((uint64_t)sum_ctx);
+            const int64_t t_end = t + dt;
+            lo_mod = emission(t_end);
+            whole = whole && all_emit;
+            t = t_end;
+            iters++;
+            steps++;
+            reqiters += cnt;
+            tokens += used;
+            if (iters > max_iters) {
+                fail(S_ELIVELOCK);
+                return;
+            }
+        }
+        if constexpr (CL) last_done = completed - c0;
+        arr_min_pk = ~0ull;
+        const bool edited = maintenance(lo_mod);
+        // Does the next formation take every resident, one token each, and
+        // nothing else (as far as the KV budget allows: see streak)? It does
+        // if the batch was whole and nothing waits. With requests waiting it
+        // does if the batch was whole, nothing completed, no key moved and
+        // the list kept its waiting entries: a waiting candidate the next
+        // formation meets with admissions open met them in this formation
+        // too, did not fit and found no eligible victim; the KV held before
+        // it has not shrunk, its own chunk has not shrunk, and the residents
+        // after it are the same with the same keys and eligibility, so it
+        // closes admissions again. Keys that all fall together (SRPT, TRAIL)
+        // only take residents from behind a waiting candidate to before it,
+        // where they hold the same KV and are no victims, so those batches
+        // repeat too. Sarathi's, which all move to the latest time, do as
+        // long as no waiting request ranks before them (it takes no victims
+        // by priority). LAS's grow, past the waiting ones: excluded.
+        bool ok = stays && completed == c0 && pol != P_LAS && arrivals_keep(next0, sp0);
+        if (lo_mod != INT32_MAX && pol != P_SRPT && pol != P_TRAIL) {
+            if constexpr (EXT) ok = ok && pol == P_SARATHI;
+            else ok = false;
+        }
+        if constexpr (EXT) {
+            if (ok && whole && pol == P_SARATHI && nW > 0) ok = resident_first();
+        }
+        rep = whole && nR > 0 && ((nW == 0 && spill_n == 0) || ok);
+        if (rep && (edited || emit_all || next != next0)) resident_chunks();
+        if constexpr (kCheck) {
+            if (status == 0) check_state();
+        }
+    }
+
     DEV void run() {
         load_pf();
         take_arrivals();
@@ -1715,78 +2114,7 @@ struct Sim {
                 take_arrivals();
                 continue;
             }
-            if constexpr (EXT) {
-                if (ad) {
-                    ada_update();
-                    if (status) break;
-                }
-            }
-            const int64_t ev0 = ev_vol + ev_forced;
-            const bool rp = rep;
-            if (rp) {
-                // the previous batch again: every resident, one token each
-                // (its context grows by one token per member)
-                U += du_next;
-                cnt = nR;
-                used = nR;
-                sum_ctx += nR;
-            } else {
-                formation();
-                if (status) break;
-                if (cnt == 0) {
-                    fail(S_ESTATE);
-                    break;
-                }
-            }
-            if constexpr (kCheck) {
-                check_batch();
-                if (status) break;
-            }
-            // formation evicted nothing, refilled nothing, stopped short of
-            // the token budget and took every resident
-            const bool rep_form = ev_vol + ev_forced == ev0 && !emit_all && used < T && cnt == nR;
-            if (U > maxU) maxU = U;
-            const int64_t dt = (int64_t)base + (int64_t)tok * used + (int64_t)ctx_quot((uint64_t)sum_ctx);
-            const int64_t t_end = t + dt;
-            const int c0 = completed;
-            const int lo_mod = emission(t_end, rp ? (G_INB | G_RES) : G_INB, rp ? 1 : 0);
-            t = t_end;
-            iters++;
-            reqiters += cnt;
-            tokens += used;
-            if (iters > max_iters) {
-                fail(S_ELIVELOCK);
-                break;
-            }
-            // Every member emitted (so every resident needs one token), none
-            // completed or moved, the list needs no repair and the next
-            // step's KV growth fits: then the next formation takes the same
-            // residents and nothing else, as long as no request arrives. A
-            // waiting candidate it meets with admissions open met them in
-            // this formation too, did not fit and found no eligible victim;
-            // the KV held by the members before it has not shrunk, its own
-            // chunk has not shrunk, and the residents after it are the same
-            // with the same keys and eligibility, so it closes admissions
-            // again. (Adaptive gamma may re-key at the next step: excluded.)
-            bool nrep = rep_form && all_emit && completed == c0 && lo_mod == INT32_MAX &&
-                        L <= cap_now() && U + du_next <= Kb;
-            if constexpr (EXT) nrep = nrep && ad == nullptr;
-            // Arrivals (merged on chip or sent to the spill) that rank after
-            // the candidate that closed admissions are met after it closes
-            // them again, and skipped: the batch still repeats, as long as
-            // nothing was spilled to make room (the on-chip list keeps every
-            // waiting entry it had). The members' chunks are recounted, as
-            // the merged arrivals may shift them. (Fixed build only: its
-            // registers would cost the extended build occupancy.)
-            const int next0 = next, sp0 = n_spilled;
-            arr_min_pk = ~0ull;
-            maintenance(lo_mod);
-            rep = nrep && (next == next0 || (!EXT && arr_min_pk > close_pk && n_spilled == sp0 &&
-                                             close_pk != ~0ull));
-            if (!EXT && rep && next != next0) resident_chunks();
-            if constexpr (kCheck) {
-                if (status == 0) check_state();
-            }
+            step(INT64_MAX);
         }
         finish();
     }
@@ -1797,7 +2125,13 @@ struct Sim {
     // With limit = INT64_MAX it runs to the end of what was dispatched.
     DEV void run_until(int64_t limit) {
         if (status) return;
+        const int next0 = next, sp0 = n_spilled;
+        arr_min_pk = ~0ull;
         take_arrivals();  // the router may have dispatched since the last call
+        if (next != next0) {
+            rep = rep && arrivals_keep(next0, sp0);
+            if (rep) resident_chunks();
+        }
         for (;;) {
             if (status) return;
             if (UNLIKELY(nW + nR == 0)) {
@@ -1824,38 +2158,7 @@ struct Sim {
                 continue;
             }
             if (t >= limit) return;
-            if (ad) {  // each replica adapts its own gamma
-                ada_update();
-                if (status) return;
-            }
-            formation();
-            if (status) return;
-            if (cnt == 0) {
-                fail(S_ESTATE);
-                return;
-            }
-            if constexpr (kCheck) {
-                check_batch();
-                if (status) return;
-            }
-            if (U > maxU) maxU = U;
-            const int64_t dt = (int64_t)base + (int64_t)tok * used + (int64_t)ctx_quot((uint64_t)sum_ctx);
-            const int64_t t_end = t + dt;
-            const int c0 = completed;
-            const int lo_mod = emission(t_end, G_INB, 0);
-            last_done = completed - c0;
-            t = t_end;
-            iters++;
-            reqiters += cnt;
-            tokens += used;
-            if (iters > max_iters) {
-                fail(S_ELIVELOCK);
-                return;
-            }
-            maintenance(lo_mod);
-            if constexpr (kCheck) {
-                if (status == 0) check_state();
-            }
+            step(limit);
         }
     }
 
@@ -1933,11 +2236,14 @@ struct Sim {
             cn[0] = iters, cn[1] = reqiters, cn[2] = tokens, cn[3] = ev_vol;
             cn[4] = ev_forced, cn[5] = t, cn[6] = maxU, cn[7] = idle;
             // the next launch's order key: the loop steps this wave ran,
-            // weighted by their measured cost (an iteration's fixed work 4,
-            // a formation pass over up to 64 candidates 5, an emission chunk
-            // 3). Unlike wall-clock time it does not depend on the slot the
-            // instance ran in.
-            if (A.work) A.work[inst] = 4 * iters + 5 * (int64_t)fpass + 3 * (int64_t)echunks;
+            // weighted by their measured cost (a step's fixed work 4, a
+            // formation pass over up to 64 candidates 5, an emission chunk
+            // 3), and far below them the iterations themselves, which a run
+            // of repeated ones takes at once. Unlike wall-clock time it does
+            // not depend on the slot the instance ran in.
+            if (A.work)
+                A.work[inst] = 4 * iters + 64 * (4 * (int64_t)steps + 5 * (int64_t)fpass +
+                                                 3 * (int64_t)echunks);
             if constexpr (EXT) {  // (zero from tas_create for the other build)
                 A.gamma_out[inst] = ad ? S.as->gamma : 0.0;
                 A.switch_out[inst] = ad ? S.as->switches : 0;

@@ -1,0 +1,116 @@
+"""Runs of repeated iterations applied in one pass: parity with the oracle
+where a run can end or must not start.
+
+Each case puts one event on the edges of a run: completions, level crossings
+(alone and together with a completion), arrivals at the very end of an
+iteration, KV budgets that the next blocks just fill, iteration costs and
+context sums past the pass's 32-bit range, the iteration limit, LTR+
+promotions and demotions, and the grid changes of adaptive gamma. All results
+are whole numbers (and gamma, compared by its bits): equality is exact.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2606_18431_amd import workloads as W
+from test_gpu_parity import assert_parity, edge_workload, gpu_run, torch  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+ADA = dict(W.ADA, window=16, min_samples=4, beta=0.3)
+POLICIES = [W.setting(0, W.FCFS), W.setting(0, W.SRPT), W.setting(0, W.LAS), W.setting(0, W.TRAIL),
+            W.setting(0, W.BOOST, gamma=1e-3, **W.UNIBOOST),
+            W.setting(0, W.BOOST, gamma=1e-3, k=3, memguard=1, delta_us=5000),
+            W.setting(0, W.BOOST, gamma=1e-3, **W.VANILLA),
+            W.setting(0, W.DIST, gamma=1e-3), W.setting(0, W.SARATHI),
+            W.setting(0, W.BOOST, gamma=1e-3, signal=1, **W.VANILLA),
+            W.setting(0, W.BOOST, gamma=1e-3, signal=2, **W.VANILLA),
+            W.setting(0, W.BOOST, gamma=1e-3, ada=ADA, **W.VANILLA)]
+LTR = [W.setting(0, W.LTR, ltr=(5, 3)), W.setting(0, W.LTR, ltr=(1, 1)),
+       W.setting(0, W.LTR, ltr=(200, 70))]
+
+ENGINES = {
+    # nothing waits: runs of 64, through completions and crossings
+    "roomy": (W.Engine(), 8.0),
+    # one step's cost takes all of the clock: every run ends at an arrival
+    "slow steps": (W.Engine(iter_base_us=400_000, max_seqs=48), 4.0),
+    # full batches: waiting requests behind the last member
+    "sequence cap": (W.Engine(max_seqs=6), 60.0),
+    # admissions closed by a waiting request that does not fit
+    "kv": (W.Engine(max_seqs=24, kv_blocks=70, chunk=64, max_tokens=200), 60.0),
+    "kv, one-token blocks": (W.Engine(max_seqs=24, kv_blocks=900, block_tokens=1, chunk=64,
+                                      max_tokens=100), 60.0),
+    "kv, 24-token blocks": (W.Engine(max_seqs=24, kv_blocks=50, block_tokens=24, chunk=50,
+                                     max_tokens=128), 60.0),
+    # the batch fills the token budget exactly
+    "token budget": (W.Engine(max_seqs=8, max_tokens=8, chunk=8, kv_blocks=400), 30.0),
+    # several chunks of members
+    "wide": (W.Engine(max_seqs=200, kv_blocks=1500), 120.0),
+    # the context sum itself in the cost
+    "unit divisor": (W.Engine(iter_ctx_div=1, max_seqs=32, kv_blocks=300), 10.0),
+}
+
+
+@pytest.mark.parametrize("ltr", [False, True], ids=["policies", "ltr"])
+@pytest.mark.parametrize("name", list(ENGINES))
+def test_runs_end_where_they_must(torch, name, ltr):  # noqa: F811
+    e, rate = ENGINES[name]
+    a, p, d = W.small_random(31, 150, rate_per_s=rate, d_med=40, d_max=400)
+    w = edge_workload(a, p, d, e, LTR if ltr else POLICIES)
+    o = oracle.run(w)
+    g = gpu_run(w)
+    assert np.array_equal(g["status"], o["status"])
+    assert_parity(w, g, o, inst=np.nonzero(o["status"] == 0)[0])
+    assert np.array_equal(g["gamma"].view(np.int64), o["gamma"].view(np.int64))
+    assert np.array_equal(g["switches"], o["switches"])
+
+
+@pytest.mark.parametrize("base,P,div", [((1 << 24) - 33, 30, 1 << 20), ((1 << 24) + 5, 30, 7),
+                                        (5000, 1_150_000, 1), (5000, 1_100_000, 1)])
+def test_costs_past_the_pass(torch, base, P, div):  # noqa: F811
+    """Iterations of 2^24 us and more, by the base cost or by a context sum
+    in units of one token (15 contexts just above and just below 2^24 / 15),
+    take the ordinary path."""
+    n = 15
+    e = W.Engine(iter_base_us=base, max_seqs=n, iter_tok_us=1 if P < 100 else 0, iter_ctx_div=div,
+                 chunk=32767, max_tokens=n * 32767, kv_blocks=n * (P // 16 + 8))
+    w = edge_workload(np.arange(n), np.full(n, P), 40 + np.arange(n), e, POLICIES)
+    o = oracle.run(w)
+    assert np.all(o["status"] == 0)
+    assert_parity(w, gpu_run(w), o)
+
+
+@pytest.mark.parametrize("shift", [-1, 0, 1])
+@pytest.mark.parametrize("step", [1, 2, 63, 64, 65, 130])
+def test_arrival_at_the_end_of_an_iteration(torch, step, shift):  # noqa: F811
+    """Three requests decode alone (the cost of every iteration is known);
+    a fourth arrives `shift` us from the end of the `step`-th repeated one."""
+    e = W.Engine(max_seqs=8, iter_ctx_div=7)
+    P, D = 32, 400
+    t = e.iter_base_us + e.iter_tok_us * 3 * P + 3 * P // e.iter_ctx_div
+    for j in range(1, step + 1):
+        t += e.iter_base_us + e.iter_tok_us * 3 + 3 * (P + j) // e.iter_ctx_div
+    w = edge_workload([0, 0, 0, t + shift], [P, P, P, 50], [D, D, D - 7, 30], e, POLICIES)
+    o = oracle.run(w)
+    assert_parity(w, gpu_run(w), o)
+
+
+@pytest.mark.parametrize("limit", [40, 41, 104, 105, 168, 169, 400])
+def test_iteration_limit_inside_a_run(torch, limit):  # noqa: F811
+    """The limit ends an instance at the same iteration, run or not."""
+    w = edge_workload([0, 0], [16, 40], [limit, limit - 3], W.Engine(max_iters=limit), POLICIES)
+    o = oracle.run(w)
+    assert np.all(o["status"] == 0)
+    assert_parity(w, gpu_run(w), o)
+    w = edge_workload([0, 0], [16, 40], [limit + 1, limit], W.Engine(max_iters=limit), POLICIES)
+    assert np.array_equal(gpu_run(w)["status"], oracle.run(w)["status"])
+
+
+@pytest.mark.parametrize("D", [3, 4, 5, 6, 7, 250, 251, 253, 254, 255, 509, 510, 511])
+def test_crossing_beside_completion(torch, D):  # noqa: F811
+    """Level thresholds k 2^j at and around the last token, and two requests
+    that cross in the same iteration while a third waits."""
+    e = W.Engine(max_seqs=3, kv_blocks=80)
+    w = edge_workload([0, 0, 10, 20], [2, 2, 9, 3], [D, D + 1, D, 12], e, POLICIES)
+    o = oracle.run(w)
+    assert_parity(w, gpu_run(w), o)
