@@ -331,10 +331,13 @@ struct Sim {
     int64_t sum_ctx;
     uint64_t emit_chunks;  // 64-entry chunks holding batch members or evictions
     bool emit_all;         // ranks moved during formation: visit every chunk
-    // Repeated batch: the next iteration's formation would select every
-    // resident with one token each and nothing else (see step), so it is
-    // skipped. Emission reports whether every batch member emitted a token.
+    // Repeated batch: the next iteration's formation would select the same
+    // residents again, one token each, and nothing else (see step), so it is
+    // skipped: the first `nb` residents of the list, up to rank `last`
+    // (INT32_MAX: all of them). Emission reports whether every batch member
+    // emitted a token.
     bool rep, all_emit;
+    int nb, last;
     int nmoved;  // entries whose key the latest emission or streak moved
     // the key of the waiting candidate that closed admissions in the latest
     // formation (~0: none), the smallest key of the arrivals taken since
@@ -419,6 +422,7 @@ struct Sim {
         emit_chunks = 0;
         emit_all = false;
         rep = all_emit = false;
+        nb = 0, last = INT32_MAX;
         nmoved = 0;
         close_pk = arr_min_pk = ~0ull;
         n_spilled = 0;
@@ -1309,8 +1313,8 @@ struct Sim {
         return lo;
     }
 
-    // A run of repeated iterations (rep): the members are all the residents,
-    // each takes one token per iteration, and nothing else changes until the
+    // A run of repeated iterations (rep): the members are the first nb
+    // residents, each takes one token per iteration, and nothing else changes until the
     // first event - a completion, a key that moves otherwise than with all
     // the others (a level crossing, an LTR+ promotion or demotion), an
     // arrival, a KV budget that the next blocks would exceed, `limit`
@@ -1344,10 +1348,10 @@ struct Sim {
             const int64_t an = rl64(pa, off);
             stop = an < stop ? an : stop;
         }
-        const int64_t fixed = (int64_t)base + (int64_t)tok * nR;
-        const int64_t top = sum_ctx + (int64_t)kWave * nR;  // the context of iteration 64
+        const int64_t fixed = (int64_t)base + (int64_t)tok * nb;
+        const int64_t top = sum_ctx + (int64_t)kWave * nb;  // the context of iteration 64
         if (UNLIKELY(fixed >= (1 << 24) || (top >> 32))) return 0;
-        const uint64_t qt = ctx_quot((uint64_t)(sum_ctx + (int64_t)(lane() + 1) * nR));
+        const uint64_t qt = ctx_quot((uint64_t)(sum_ctx + (int64_t)(lane() + 1) * nb));
         if (UNLIKELY((uint32_t)rl((int)(uint32_t)qt, 63) >= (1u << 24))) return 0;
         const int cost = (int)fixed + (int)qt;
         const int tend = scan_add(cost);  // below 64 * 2^25
@@ -1367,7 +1371,7 @@ struct Sim {
             const int i = ffs0(todo) * kWave + lane();
             const uint4 q = ldq(min(i, L - 1));
             const uint32_t g = i < L ? q.x : 0u;
-            const bool res = (g & G_RES) != 0;
+            const bool memb = (g & G_RES) != 0 && i <= last;
             int e = sleft(q);
             if (pol == P_BOOST) {  // tokens to the next level's threshold k 2^(level+1)
                 const int up = (int)((g >> G_LVL_SHIFT) & 31u) + 1;
@@ -1383,22 +1387,22 @@ struct Sim {
             }
             if constexpr (EXT) {
                 if (pol == P_LTR && (g & G_PROMO)) e = min(e, max((int)(g >> kLtrShift), 1));
-                if (pol == P_LTR && i < L && !(g & (G_RES | G_DONE | G_PROMO)))
+                if (pol == P_LTR && i < L && !memb && !(g & (G_DONE | G_PROMO)))
                     ev = min(ev, ltr_s - (int)(g >> kLtrShift));
             }
-            if (res) ev = min(ev, e);
+            if (memb) ev = min(ev, e);
         }
         r = wmin(ev);
         if (r <= 0) return 0;
         // KV: every iteration's new blocks fit (the growth only adds up, so the
         // last one's total decides); halved until they do
-        while (UNLIKELY(U + (int64_t)nR * blocks(r) > Kb)) {
+        while (UNLIKELY(U + (int64_t)nb * blocks(r) > Kb)) {
             int grow = 0;
             for (uint64_t todo = emit_chunks; todo; todo &= todo - 1) {
                 const int i = ffs0(todo) * kWave + lane();
                 const uint4 q = ldq(min(i, L - 1));
                 const int kv = skv(q);
-                if (i < L && (q.x & G_RES)) grow += blocks(kv + r) - blocks(kv);
+                if (i < L && i <= last && (q.x & G_RES)) grow += blocks(kv + r) - blocks(kv);
             }
             if ((int64_t)U + wsum(grow) <= Kb) break;
             r >>= 1;
@@ -1422,7 +1426,7 @@ struct Sim {
             const uint4 q = ldq(i0);
             const uint2 tg = S.tg[i0];
             const uint32_t g = i < L ? q.x : 0u;
-            const bool memb = (g & G_RES) != 0;
+            const bool memb = (g & G_RES) != 0 && i <= last;
             const int w = sw(q) + r, left = sleft(q) - r;
             int kv = skv(q);
             grow += memb ? blocks(kv + r) - blocks(kv) : 0;
@@ -1476,11 +1480,11 @@ struct Sim {
                     }
                 }
             } else if (pol == P_SRPT || pol == P_TRAIL || pol == P_LAS) {
-                // every member's key moves by r; holes move along, so that the
-                // residents and holes stay in order
+                // every member's key moves by r; holes among them move along, so
+                // that the residents and holes stay in order
                 const uint64_t d = (uint64_t)(uint32_t)r << kIdxBits;
                 const uint64_t pk = S.k[i0];
-                if (memb || (g & G_DONE)) S.k[i] = pol == P_LAS ? pk + d : pk - d;
+                if (memb || ((g & G_DONE) && i <= last)) S.k[i] = pol == P_LAS ? pk + d : pk - d;
                 // past a waiting entry, perhaps: compaction finds those
                 if (pol != P_LAS && nW > 0) cm = ballot(memb && !fin);
             }
@@ -1503,7 +1507,7 @@ struct Sim {
                         } else {
                             gs -= (uint32_t)r << kLtrShift;
                         }
-                    } else if (i < L && !(g & (G_RES | G_DONE | G_PROMO))) {
+                    } else if (i < L && !memb && !(g & (G_DONE | G_PROMO))) {
                         const uint32_t c2 = (g >> kLtrShift) + (uint32_t)r;
                         uint32_t gx = (g & G_FLAGS) | (c2 << kLtrShift);
                         if ((int)c2 >= ltr_s) {  // promoted at the end of the r-th iteration
@@ -1529,9 +1533,9 @@ struct Sim {
         wsync();
         if (pol == P_TRAIL) vm_ok = false;  // eligibility depends on progress
         iters += r;
-        reqiters += (int64_t)r * nR;
-        tokens += (int64_t)r * nR;
-        sum_ctx += (int64_t)r * nR;
+        reqiters += (int64_t)r * nb;
+        tokens += (int64_t)r * nb;
+        sum_ctx += (int64_t)r * nb;
         U += wsum(grow);
         if (U > maxU) maxU = U;
         if (nd) {
@@ -1687,15 +1691,25 @@ struct Sim {
         wsync();
     }
 
-    // emit_chunks := the 64-entry chunks holding residents (in a repeated
-    // batch, every resident is a member)
-    DEV void resident_chunks() {
+    // The members of a repeated batch: emit_chunks := the 64-entry chunks
+    // holding the first nb residents; returns the rank of the last of them.
+    DEV int find_members() {
         uint64_t m = 0;
+        int left = nb, at = -1;
         for (int b = 0; b < L; b += kWave) {
             const int r = b + lane();
-            if (ballot(r < L && (ldx(r) & G_RES))) m |= 1ull << (b >> 6);
+            const bool res = r < L && (ldx(r) & G_RES);
+            const uint64_t rm = ballot(res);
+            if (!rm) continue;
+            m |= 1ull << (b >> 6);
+            if (popc(rm) >= left) {
+                at = b + ffs0(ballot(res && mbcnt(rm) == left - 1));
+                break;
+            }
+            left -= popc(rm);
         }
         emit_chunks = m;
+        return at;
     }
 
     // Returns whether entries may have moved to other ranks.
@@ -1984,13 +1998,23 @@ struct Sim {
 
     // ---------------------------------------------------------- driver
 
-    // Nothing arrived since `next0`, or all that arrived is met after the
-    // waiting candidate that closed admissions, and so skipped, and nothing
-    // was spilled to make room (the on-chip list keeps every waiting entry it
-    // had): the arrivals do not change a repeated batch.
-    DEV bool arrivals_keep(int next0, int sp0) const {
-        return n_spilled == sp0 &&
-               (next == next0 || (close_pk != ~0ull && arr_min_pk > close_pk));
+    // Whether a batch that repeats but for the requests that arrived since
+    // `next0` still does: those are met after admissions close, or not at
+    // all because the batch is full before them, or nothing arrived. Finds
+    // the members again where ranks may have moved (`moved`).
+    DEV bool arrivals_keep(int next0, bool moved) {
+        const bool full = nb == M;
+        last = INT32_MAX;
+        uint64_t bar = close_pk;
+        if (moved || full) {
+            const int at = find_members();
+            if (full && at >= 0) {
+                last = at;
+                const uint64_t pk = uniu(S.k[at]);
+                bar = pk < bar ? pk : bar;
+            }
+        }
+        return next == next0 || (bar != ~0ull && arr_min_pk > bar);
     }
 
     // Sarathi: the first live entry of the list is a resident, so no waiting
@@ -2001,7 +2025,9 @@ struct Sim {
             const int i = b + lane();
             const uint32_t g = i < L ? ldx(i) : G_DONE;
             const uint64_t live = ballot(!(g & G_DONE)), res = ballot((g & G_RES) != 0);
-            if (live) return (res >> ffs0(live)) & 1ull;
+            if (live)
+                return ((res >> ffs0(live)) & 1ull) &&
+                       (spill_n == 0 || spill_min > uniu(S.k[b + ffs0(live)]));
         }
         return false;
     }
@@ -2012,9 +2038,11 @@ struct Sim {
         pin();
         const int c0 = completed, next0 = next, sp0 = n_spilled;
         int lo_mod = INT32_MAX;
-        // whole: the batch held every resident and each emitted a token, so
-        // each needs exactly one next; stays: see below
-        bool whole = true, stays = true;
+        // Does the next iteration repeat this one's batch? `again`: every
+        // member emitted a token, so each needs exactly one next; `whole`:
+        // the members are all the residents; `stays`: formation evicted
+        // nothing, refilled nothing and stopped short of the token budget.
+        bool again = true, whole = last == INT32_MAX || nb == nR, stays = true;
         if (!(rep && streak(limit, lo_mod) > 0)) {
             if constexpr (EXT) {
                 if (ad) {
@@ -2034,15 +2062,14 @@ struct Sim {
                 if (status) return;
             }
             whole = cnt == nR;
-            // formation evicted nothing, refilled nothing and stopped short
-            // of the token budget
+            nb = cnt;
             stays = ev_vol + ev_forced == ev0 && !emit_all && used < T;
             if (U > maxU) maxU = U;
             const int64_t dt =
                 (int64_t)base + (int64_t)tok * used + (int64_t)ctx_quot((uint64_t)sum_ctx);
             const int64_t t_end = t + dt;
             lo_mod = emission(t_end);
-            whole = whole && all_emit;
+            again = all_emit;
             t = t_end;
             iters++;
             steps++;
@@ -2056,31 +2083,41 @@ struct Sim {
         if constexpr (CL) last_done = completed - c0;
         arr_min_pk = ~0ull;
         const bool edited = maintenance(lo_mod);
-        // Does the next formation take every resident, one token each, and
-        // nothing else (as far as the KV budget allows: see streak)? It does
-        // if the batch was whole and nothing waits. With requests waiting it
-        // does if the batch was whole, nothing completed, no key moved and
+        // A whole batch repeats (as far as the KV budget allows: see streak)
+        // if nothing waits. With requests waiting, or residents left out of
+        // a full batch, it repeats if nothing completed, no key moved and
         // the list kept its waiting entries: a waiting candidate the next
         // formation meets with admissions open met them in this formation
         // too, did not fit and found no eligible victim; the KV held before
         // it has not shrunk, its own chunk has not shrunk, and the residents
         // after it are the same with the same keys and eligibility, so it
-        // closes admissions again. Keys that all fall together (SRPT, TRAIL)
-        // only take residents from behind a waiting candidate to before it,
-        // where they hold the same KV and are no victims, so those batches
-        // repeat too. Sarathi's, which all move to the latest time, do as
-        // long as no waiting request ranks before them (it takes no victims
-        // by priority). LAS's grow, past the waiting ones: excluded.
-        bool ok = stays && completed == c0 && pol != P_LAS && arrivals_keep(next0, sp0);
+        // closes admissions again. A full batch (max_seqs) ends the
+        // formation at its last member. Keys that all fall together (SRPT,
+        // TRAIL) only take residents from behind a waiting candidate to
+        // before it, where they hold the same KV and are no victims, so those
+        // batches repeat too. Sarathi's, which all move to the latest time,
+        // do as long as no resident is left out and no waiting request ranks
+        // before them (it takes no victims by priority). LAS's grow, past
+        // the waiting ones: excluded.
+        const bool alone = whole && nW == 0 && spill_n == 0;
+        bool ok = stays && completed == c0 && pol != P_LAS && n_spilled == sp0 &&
+                  (whole || nb == M);
         if (lo_mod != INT32_MAX && pol != P_SRPT && pol != P_TRAIL) {
             if constexpr (EXT) ok = ok && pol == P_SARATHI;
             else ok = false;
         }
         if constexpr (EXT) {
-            if (ok && whole && pol == P_SARATHI && nW > 0) ok = resident_first();
+            if (ok && pol == P_SARATHI && !alone) ok = whole && resident_first();
         }
-        rep = whole && nR > 0 && ((nW == 0 && spill_n == 0) || ok);
-        if (rep && (edited || emit_all || next != next0)) resident_chunks();
+        rep = again && nR > 0 && (alone || ok);
+        if (rep) {
+            if (alone) {
+                nb = nR, last = INT32_MAX;
+                if (edited || emit_all || next != next0) find_members();
+            } else {
+                rep = arrivals_keep(next0, edited || emit_all || next != next0);
+            }
+        }
         if constexpr (kCheck) {
             if (status == 0) check_state();
         }
@@ -2128,10 +2165,7 @@ struct Sim {
         const int next0 = next, sp0 = n_spilled;
         arr_min_pk = ~0ull;
         take_arrivals();  // the router may have dispatched since the last call
-        if (next != next0) {
-            rep = rep && arrivals_keep(next0, sp0);
-            if (rep) resident_chunks();
-        }
+        if (rep && next != next0) rep = n_spilled == sp0 && arrivals_keep(next0, true);
         for (;;) {
             if (status) return;
             if (UNLIKELY(nW + nR == 0)) {
