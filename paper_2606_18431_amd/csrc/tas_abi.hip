@@ -48,7 +48,7 @@ int32_t replicas_of(const tas_params *p) { return p->jsq_replicas > 1 ? p->jsq_r
 // Dynamic LDS of a launch: one list per instance, or the router block and
 // one 16-aligned list per replica (replicas use four-word slots).
 int64_t launch_lds(int32_t list_cap, int32_t wmax, int32_t replicas, bool compact) {
-    if (replicas <= 1) return tas::lds_bytes_for(list_cap, wmax, compact);
+    if (replicas <= 1) return tas::kTallyBytes + tas::lds_bytes_for(list_cap, wmax, compact);
     const int64_t one = tas::lds_bytes_for(list_cap, wmax);
     return tas::kJsqLdsBytes + (int64_t)replicas * ((one + 15) & ~int64_t(15));
 }
@@ -104,8 +104,8 @@ int32_t default_list_cap(int32_t max_seqs, bool adaptive, bool compact) {
     const int64_t lo = (int64_t)max_seqs + 64, hi = (int64_t)max_seqs + 128;
     for (const int64_t per_cu : {16, 12}) {
         int64_t l = hi;
-        while (l >= lo && tas::lds_bytes_for((int32_t)std::min<int64_t>(l, tas::kMaxListCap), 0,
-                                             compact) * per_cu > kMaxLds)
+        while (l >= lo && launch_lds((int32_t)std::min<int64_t>(l, tas::kMaxListCap), 0, 1,
+                                     compact) * per_cu > kMaxLds)
             l = (l - 1) / 8 * 8;
         if (l >= lo) return (int32_t)std::min<int64_t>(l, tas::kMaxListCap);
     }
@@ -146,7 +146,7 @@ bool caps(const tas_traces *t, const tas_params *p, int32_t *lc, int32_t *rc, in
     int32_t r = p->retry_cap ? p->retry_cap : default_retry_cap(l);
     if (r < l) r = l;
     while (r > l && launch_lds(r, wmax, nr, compact) > kMaxLds) r -= 64;  // room for the window
-    if (r > tas::kMaxListCap || tas::lds_bytes_for(r, wmax, compact) > kMaxLds) return false;
+    if (r > tas::kMaxListCap || launch_lds(r, wmax, 1, compact) > kMaxLds) return false;
     *lc = l;
     *rc = r;
     *sc = p->spill_cap ? p->spill_cap : t->n_req;

@@ -112,6 +112,11 @@ inline int64_t ada_lds_bytes(int32_t window) {
     return window > 0 ? kAdaStateBytes + int64_t(window) * 8 : 0;
 }
 
+// Counters of one instance in LDS: request-iterations, tokens, evictions (two
+// kinds), loop steps, idle time. (A replica's are in its router block.)
+constexpr int kTally = 6;
+constexpr int64_t kTallyBytes = kTally * 8;
+
 // LDS bytes per candidate-list slot: the packed key (8 B), the last token
 // time and gap maximum (8 B), and the state {gs, w, kv, left} in 16 B, or in
 // 8 B with compact slots.

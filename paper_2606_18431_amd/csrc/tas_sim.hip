@@ -108,10 +108,24 @@ DEV uint64_t rlu(uint64_t x, int l) {
 }
 DEV int64_t rl64(int64_t x, int l) { return (int64_t)rlu((uint64_t)x, l); }
 DEV uint64_t uniu(uint64_t x) { return rlu(x, __builtin_amdgcn_readfirstlane(lane())); }
+// A wave-uniform 64-bit value in scalar registers: 64-bit comparisons, and the
+// selects on them, have no scalar form, and a value that came out of one would
+// otherwise stay in vector registers around the whole loop.
 DEV uint64_t sgpr64(uint64_t x) {
     const uint32_t lo = (uint32_t)uni((int)(uint32_t)x), hi = (uint32_t)uni((int)(uint32_t)(x >> 32));
     return ((uint64_t)hi << 32) | lo;
 }
+// x with lane LANE set to the wave-uniform v
+template <int LANE>
+DEV int set_lane(int x, int v) {
+    __asm__("v_writelane_b32 %0, %1, %2" : "+v"(x) : "s"(uni(v)), "n"(LANE));
+    return x;
+}
+// x < y for wave-uniform values whose difference fits 63 bits, in scalar
+// instructions.
+DEV bool less64(int64_t x, int64_t y) { return (int)((uint64_t)(x - y) >> 63) != 0; }
+// min(d, 2^31 - 1) for d >= 0, likewise
+DEV int sat31(int64_t d) { return ((uint64_t)d >> 31) ? INT32_MAX : (int)d; }
 // One wavefront is the whole workgroup and its LDS operations execute in
 // issue order, so ordering LDS traffic between lanes only needs the compiler
 // not to move memory operations across this point.
@@ -216,9 +230,13 @@ struct Lds {
     uint64_t *k;
     uint2 *tg;
     int64_t *bt;
+    uint64_t *ty;  // Tally
     struct AdaLds *as;  // adaptive gamma: state, then the window in completion
     uint32_t *wr, *ws;  // order (a ring) and sorted
 };
+
+// Counters of one instance, kept in LDS (of a replica: in its router block).
+enum Tally { TY_REQITERS, TY_TOKENS, TY_EVVOL, TY_EVFORCED, TY_WORK, TY_IDLE };
 
 // Adaptive-gamma state of one instance (LDS, written by lane 0).
 struct AdaLds {
@@ -300,32 +318,27 @@ struct Sim {
     const SimArgs &A;
     Lds S;
     // instance constants (memguard and delta are zero unless pol is BOOST)
-    int inst, N, M, T, c, Kb, bs, base, tok, div, pol, k, lk, memguard, lcap, scap;
+    int inst, trace, N, M, Kb, bs, pol, k, lk, memguard, lcap;
     int ltr_s, ltr_q;  // LTR+: starvation threshold and quantum (iterations)
-    int64_t delta, max_iters;
-    uint64_t div_magic;  // ceil(2^64 / div) for div >= 2
-    const int64_t *arr;
-    const int32_t *Pp, *Dp;
-    int64_t *tfirst, *tlast;
-    uint32_t *tbo;  // the instance's max-gap outputs, written at completion
-    Rec *spill, *ovf;
-    // state
+    int64_t delta;
+    // state. It has to stay in scalar registers through every loop: the
+    // compiler copies all of it wherever paths meet, and what does not fit is
+    // moved to vector lanes and back. So the counters live in LDS (Tally),
+    // 64-bit values see no comparison or select, and addresses used now and
+    // then are read from the kernel arguments each time (args).
     int64_t t;
     int U, L, nW, nR, n_holes, lo_hole, spill_n, next, pf, completed, status;
     uint64_t spill_min;
     int64_t pa;
     int pP, pD;
-    int64_t iters, reqiters, tokens, ev_vol, ev_forced, maxU, idle;
-    // loop steps for the launch-order key: steps (an iteration, or a run of
-    // repeated ones), formation passes and emission chunks (32-bit: a wrap
-    // only perturbs the order of a huge instance)
-    uint32_t steps, fpass, echunks;
+    int64_t iters;
+    int maxU;
+    int ev_vol, ev_forced, fpass;  // evictions and passes of the latest formation
     // CL: the replica (wave) index, the global indices dispatched to it in
     // order (HBM, written and read by this wave only, through L2), how many,
     // the prefetched global index of each lane, and the completions of the
     // latest iteration
     int wv, Nk, pidx, last_done;
-    int32_t *jl;
     // per-iteration formation results
     int cnt, used;
     int64_t sum_ctx;
@@ -338,11 +351,12 @@ struct Sim {
     // emitted a token.
     bool rep, all_emit;
     int nb, last;
+    int n_chunks;  // chunks the latest emission visited
     int nmoved;  // entries whose key the latest emission or streak moved
     // the key of the waiting candidate that closed admissions in the latest
-    // formation (~0: none), the smallest key of the arrivals taken since
-    // (~0: none) and a count of spill_excess calls
-    uint64_t close_pk, arr_min_pk;
+    // formation (~0: none), the smallest keys of the arrivals taken since
+    // (per lane, ~0: none) and a count of spill_excess calls
+    uint64_t close_pk, arr_pk;
     int n_spilled;
     // victim masks, lane c = chunk c: residents, and those a voluntary
     // eviction may take (MemGuard). Kept across iterations: bits change in
@@ -356,30 +370,48 @@ struct Sim {
     double bnd;
     bool phase_signal;  // BOOST with Algorithm 2's signal: P in prefill, dec after
     bool cache_signal;  // BOOST with the cache-aware signal P - h + dec
-    const int32_t *Hp;  // expected prefix-cache hits of the trace (cache_signal)
 
-    DEV Sim(const SimArgs &a, const DevSetting &st, int i, unsigned char *smem, int w = 0) : A(a) {
-        inst = i;
-        N = a.n_req, M = a.M, T = a.T, c = a.c, Kb = a.Kb, bs = a.bs;
-        base = a.base, tok = a.tok, div = a.div, lcap = a.list_cap, scap = a.spill_cap;
+    // The kernel's arguments, read again where they are used: addresses
+    // needed a few times per request are not worth registers all the time.
+    typedef const __attribute__((address_space(4))) SimArgs KArgs;
+    DEV KArgs *args() const {
+        uint64_t p = sgpr64((uint64_t)__builtin_amdgcn_kernarg_segment_ptr());
+        __asm__ volatile("" : "+s"(p));  // a new value each time: nothing to keep
+        return (KArgs *)p;
+    }
+    DEV size_t toff() const { return (size_t)trace * (size_t)N; }
+    DEV size_t ioff() const { return (size_t)inst * (size_t)N; }
+    DEV size_t slot() const {
+        return CL ? (size_t)inst * (size_t)args()->replicas + (size_t)wv : (size_t)inst;
+    }
+    DEV const int64_t *arr() const { return args()->arrival + toff(); }
+    DEV const int32_t *Pp() const { return args()->prompt + toff(); }
+    DEV const int32_t *Dp() const { return args()->decode + toff(); }
+    // expected prefix-cache hits of the trace (cache_signal)
+    DEV const int32_t *Hp() const { return args()->cached + toff(); }
+    DEV int64_t *tfirst() const { return args()->tfirst + ioff(); }
+    DEV int64_t *tlast() const { return args()->tlast + ioff(); }
+    // the instance's max-gap outputs, written at completion
+    DEV uint32_t *tbo() const { return args()->tbtmax + ioff(); }
+    DEV Rec *spill() const { return args()->spill + slot() * (size_t)scap(); }
+    DEV int scap() const { return args()->spill_cap; }
+    DEV Rec *ovf() const { return args()->ovf + slot() * (size_t)args()->ovf_stride; }
+    DEV int32_t *jl() const { return args()->jidx + slot() * (size_t)N; }
+
+    DEV Sim(const SimArgs &a, const DevSetting &st, int i, unsigned char *smem, uint64_t *tally,
+            int w = 0)
+        : A(a) {
+        inst = i, trace = st.trace;
+        N = a.n_req, M = a.M, Kb = a.Kb, bs = a.bs, lcap = a.list_cap;
         k = st.k > 0 ? st.k : 1;
         lk = 31 - __clz(k);
         pol = st.policy;
         ltr_s = st.ltr_s, ltr_q = st.ltr_q;
         memguard = st.memguard;
         delta = st.delta;
-        max_iters = a.max_iters;
-        div_magic = a.div_magic;
-        const size_t toff = (size_t)st.trace * (size_t)N;
-        arr = a.arrival + toff, Pp = a.prompt + toff, Dp = a.decode + toff;
-        const size_t ioff = (size_t)i * (size_t)N;
-        tfirst = a.tfirst + ioff, tlast = a.tlast + ioff, tbo = a.tbtmax + ioff;
         wv = w, Nk = 0, pidx = 0, last_done = 0;
-        jl = nullptr;
-        const size_t slot = CL ? (size_t)i * (size_t)a.replicas + (size_t)w : (size_t)i;
-        spill = a.spill + slot * (size_t)scap;
-        ovf = a.ovf + slot * (size_t)a.ovf_stride;
-        if constexpr (CL) jl = a.jidx + slot * (size_t)N;
+        S.ty = tally;
+        if (lane() < kTally) S.ty[lane()] = 0;
         const int cap = lcap + kStage;  // the list may use its overflow region during formation
         size_t o = 0;
         S.q = nullptr, S.q2 = nullptr;
@@ -393,7 +425,6 @@ struct Sim {
         bnd = 0.0;
         phase_signal = EXT && st.signal == 1;
         cache_signal = EXT && st.signal == 2;
-        Hp = cache_signal ? a.cached + toff : nullptr;
         if constexpr (EXT) {
             S.as = (AdaLds *)(smem + o), o += kAdaStateBytes;
             S.wr = (uint32_t *)(smem + o), o += (size_t)a.ada_window * 4;
@@ -415,42 +446,36 @@ struct Sim {
         U = L = nW = nR = n_holes = spill_n = next = pf = completed = status = 0;
         lo_hole = INT32_MAX;
         spill_min = ~0ull;
-        iters = reqiters = tokens = ev_vol = ev_forced = maxU = idle = 0;
-        steps = fpass = echunks = 0;
+        iters = 0, maxU = 0;
+        ev_vol = ev_forced = fpass = 0;
         cnt = used = 0;
         sum_ctx = 0;
         emit_chunks = 0;
         emit_all = false;
         rep = all_emit = false;
         nb = 0, last = INT32_MAX;
-        nmoved = 0;
-        close_pk = arr_min_pk = ~0ull;
+        nmoved = 0, n_chunks = 0;
+        close_pk = arr_pk = ~0ull;
         n_spilled = 0;
         vm_res = vm_ev = 0;
         vm_ok = false;
         wsync();
     }
 
-    // The wave-uniform state back in scalar registers: 64-bit comparisons and
-    // selects have no scalar form here, and values that pass through one
-    // would otherwise live in vector registers around the whole loop.
-    DEV void pin() {
-        t = (int64_t)sgpr64((uint64_t)t);
-        sum_ctx = (int64_t)sgpr64((uint64_t)sum_ctx);
-        iters = (int64_t)sgpr64((uint64_t)iters);
-        reqiters = (int64_t)sgpr64((uint64_t)reqiters);
-        tokens = (int64_t)sgpr64((uint64_t)tokens);
-        ev_vol = (int64_t)sgpr64((uint64_t)ev_vol);
-        ev_forced = (int64_t)sgpr64((uint64_t)ev_forced);
-        maxU = (int64_t)sgpr64((uint64_t)maxU);
-        idle = (int64_t)sgpr64((uint64_t)idle);
-        spill_min = sgpr64(spill_min);
-        close_pk = sgpr64(close_pk);
-        arr_min_pk = sgpr64(arr_min_pk);
-        emit_chunks = sgpr64(emit_chunks);
-        U = uni(U), L = uni(L), nW = uni(nW), nR = uni(nR), n_holes = uni(n_holes);
-        lo_hole = uni(lo_hole), spill_n = uni(spill_n), next = uni(next), pf = uni(pf);
-        completed = uni(completed), status = uni(status), n_spilled = uni(n_spilled);
+    // Adds to the counters in LDS (per step: below 2^32 each): lane j adds to
+    // counter j, nothing waits for it.
+    DEV void tally(int req, int tok_, int work) const {
+        int v = 0;
+        v = set_lane<TY_REQITERS>(v, req);
+        v = set_lane<TY_TOKENS>(v, tok_);
+        v = set_lane<TY_WORK>(v, work);
+        if (ev_vol + ev_forced) {
+            v = set_lane<TY_EVVOL>(v, ev_vol);
+            v = set_lane<TY_EVFORCED>(v, ev_forced);
+        }
+        if (lane() <= TY_WORK)
+            __hip_atomic_fetch_add(&S.ty[lane()], (uint64_t)(uint32_t)v, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
     }
 
     DEV void fail(int code) {
@@ -521,13 +546,25 @@ struct Sim {
             return lcap;
         }
     }
-    // floor(s / div). Below 2^32 a multiply by the rounded-up reciprocal is
-    // exact: s * ceil(2^64/div) / 2^64 exceeds s/div by less than 2^-32 <= 1/div.
-    DEV uint64_t ctx_quot(uint64_t s) const {
-        if (div == 1) return s;
-        if (s >> 32) return s / (uint64_t)div;
-        const uint32_t x = (uint32_t)s;
-        return ((uint64_t)x * (div_magic >> 32) + __umulhi(x, (uint32_t)div_magic)) >> 32;
+    // The cost model, read from the kernel arguments (see args).
+    struct Cost {
+        int base, tok, div;
+        uint64_t div_magic;  // ceil(2^64 / div) for div >= 2
+        // floor(s / div). Below 2^32 a multiply by the rounded-up reciprocal is
+        // exact: s * ceil(2^64/div) / 2^64 exceeds s/div by less than 2^-32 <= 1/div.
+        DEV uint64_t quot(uint64_t s) const {
+            if (div == 1) return s;
+            if (s >> 32) return s / (uint64_t)div;
+            const uint32_t x = (uint32_t)s;
+            return ((uint64_t)x * (div_magic >> 32) + __umulhi(x, (uint32_t)div_magic)) >> 32;
+        }
+        DEV int64_t fixed(int tokens) const { return (int64_t)base + (int64_t)tok * tokens; }
+    };
+    DEV Cost cost_model() const {
+        KArgs *a = args();
+        Cost c;
+        c.base = a->base, c.tok = a->tok, c.div = a->div, c.div_magic = a->div_magic;
+        return c;
     }
     DEV int blocks(int x) const {
         if constexpr (BSH >= 0) {
@@ -547,10 +584,10 @@ struct Sim {
         const int r = pf + lane();
         if (r < n_known()) {
             if constexpr (CL) {
-                pidx = __hip_atomic_load(&jl[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                pa = arr[pidx], pP = Pp[pidx], pD = Dp[pidx];
+                pidx = __hip_atomic_load(&jl()[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                pa = arr()[pidx], pP = Pp()[pidx], pD = Dp()[pidx];
             } else {
-                pa = arr[r], pP = Pp[r], pD = Dp[r];
+                pa = arr()[r], pP = Pp()[r], pD = Dp()[r];
             }
         } else {
             pa = INT64_MAX, pP = 1, pD = 1;
@@ -575,7 +612,7 @@ struct Sim {
             int sig = P;  // the signal before the first token
             if constexpr (EXT) {
                 // cached tokens are not work (lanes past the trace hold no request)
-                if (cache_signal && idx < N) sig = P - Hp[idx];
+                if (cache_signal && idx < N) sig = P - Hp()[idx];
             }
             lvl = (uint32_t)level_of(sig, k, lk);
             key = a - S.bt[lvl];
@@ -600,7 +637,7 @@ struct Sim {
             if (LIKELY(n_arr == 0)) return;
             const R x = new_record(CL ? pidx : r, pa, pP, pD);
             const R y = off ? shfl_rec(x, min(off + lane(), kWave - 1)) : x;
-            arr_min_pk = min(arr_min_pk, wminu(lane() < n_arr ? y.pk : ~0ull));
+            arr_pk = min(arr_pk, lane() < n_arr ? y.pk : ~0ull);
             nW += n_arr;
             next += n_arr;
             add_entries(y, n_arr);
@@ -705,7 +742,7 @@ struct Sim {
             fail(S_ECAPACITY);
             return;
         }
-        if (spill_n + E > scap) {
+        if (spill_n + E > scap()) {
             fail(S_ECAPACITY);
             return;
         }
@@ -719,7 +756,7 @@ struct Sim {
             if (take) {
                 R y;
                 ldr(r, y);
-                spill[spill_n + found + above] = to_rec(y);
+                spill()[spill_n + found + above] = to_rec(y);
                 stx(r, y.gs | G_MARK);
             }
             const uint64_t tm = ballot(take);
@@ -732,7 +769,7 @@ struct Sim {
             return;
         }
         const uint64_t mn = uniu(S.k[lowest]);
-        spill_min = (spill_n == 0 || mn < spill_min) ? mn : spill_min;
+        spill_min = sgpr64((spill_n == 0 || mn < spill_min) ? mn : spill_min);
         spill_n += E;
         nW -= E;
         compact_remove(lowest, G_MARK);
@@ -746,11 +783,11 @@ struct Sim {
             const uint64_t sm = ballot(toS);
             const int ns = popc(sm);
             if (ns) {
-                if (spill_n + ns > scap) {
+                if (spill_n + ns > scap()) {
                     fail(S_ECAPACITY);
                     return;
                 }
-                if (toS) spill[spill_n + mbcnt(sm)] = to_rec(y);
+                if (toS) spill()[spill_n + mbcnt(sm)] = to_rec(y);
                 spill_n += ns;
                 nW -= ns;
                 const uint64_t km = ballot(lane() < K && !toS);
@@ -766,6 +803,7 @@ struct Sim {
     // 16 bin counts held one per lane (no LDS histogram).
     DEV uint64_t select_kth(int want) {
         hbm_fence();
+        Rec *const spill = this->spill();
         uint64_t prefix = 0;
         int rank = want;
         for (int d = 15; d >= 0; d--) {
@@ -809,6 +847,7 @@ struct Sim {
     DEV void refill_into(int room) {
         const int want = min(spill_n, room);
         if (want <= 0) return;
+        Rec *const spill = this->spill();
         const uint64_t theta = want < spill_n ? select_kth(want) : ~0ull;
         if (status) return;
         hbm_fence();
@@ -862,7 +901,7 @@ struct Sim {
                 int64_t Dv = 0, lv = 0;
                 if (rs) {
                     const int idx = idx_of(S.k[r]);
-                    Dv = idx < N ? Dp[idx] : 0;
+                    Dv = idx < N ? Dp()[idx] : 0;
                     lv = CP ? (int)(g >> kLeftShift) + 1 : (int)S.q[r].w;
                 }
                 ev = rs && !(2 * Dv >= 5 * lv);
@@ -1020,6 +1059,7 @@ struct Sim {
 
     DEV void formation() {
         close_pk = ~0ull;
+        ev_vol = ev_forced = fpass = 0;
         cnt = 0, used = 0;
         sum_ctx = 0;
         emit_chunks = 0;
@@ -1031,13 +1071,14 @@ struct Sim {
         // the next chunk's records, loaded while this one is processed; valid
         // while formation walks whole chunks without touching the list
         const int lim = lcap + kStage;
+        const int T = args()->T, c = args()->c;
         uint4 nx = make_uint4(0u, 0u, 0u, 0u);
         bool have_nx = false;
         // every pass advances p or refills from the spill, so the walk ends
         // within L + spill_cap passes; a walk that does not is a broken state
         for (int pass = 0;; pass++) {
             fpass++;
-            if (UNLIKELY(pass > lcap + kStage + scap + 2)) {
+            if (UNLIKELY(pass > lcap + kStage + scap() + 2)) {
                 fail(S_ESTATE);
                 return;
             }
@@ -1136,7 +1177,7 @@ struct Sim {
     // Returns the lowest rank whose key moved (INT32_MAX if none).
     DEV int emission(int64_t t_end) {
         int lo = INT32_MAX, lohole = INT32_MAX, nd = 0, ufree = 0, kfree = 0, nmv = 0;
-        nmoved = 0;
+        nmoved = 0, n_chunks = 0;
         bool bad_idx = false;
         uint64_t noemit = 0;  // batch members that emitted no token
         const uint32_t t32 = (uint32_t)t_end;
@@ -1145,7 +1186,7 @@ struct Sim {
         const bool all = emit_all || (EXT && pol == P_LTR);
         uint64_t todo = all ? (nch >= 64 ? ~0ull : ((1ull << nch) - 1ull)) : emit_chunks;
         if (!todo) return INT32_MAX;
-        echunks += popc(todo);
+        n_chunks = popc(todo);
         // chunks are visited in ascending order, the next one's records loaded
         // while this one is processed (a chunk's edits stay inside it). Lanes
         // past the list end read its last slot and are masked out.
@@ -1193,10 +1234,10 @@ struct Sim {
             gs = fin ? (gs | G_DONE) & ~G_RES : gs;
             ufree += fin ? blocks(kv) : 0;
             kfree += fin ? kv : 0;
-            if (first) tfirst[idx] = t_end;
+            if (first) tfirst()[idx] = t_end;
             if (fin) {
-                tlast[idx] = t_end;
-                tbo[idx] = gm;
+                tlast()[idx] = t_end;
+                tbo()[idx] = gm;
             }
             kv = fin ? 0 : kv;
             const bool live = emit && !fin;  // emitted and has tokens left
@@ -1216,8 +1257,8 @@ struct Sim {
                 if constexpr (EXT) {
                     // every lane reads: keep non-member lanes in bounds
                     const int ix = min(idx, N - 1);
-                    if (phase_signal) sig = w - Pp[ix];  // dec >= 1 after this token
-                    if (cache_signal) sig = w - Hp[ix];  // P - h + dec
+                    if (phase_signal) sig = w - Pp()[ix];  // dec >= 1 after this token
+                    if (cache_signal) sig = w - Hp()[ix];  // P - h + dec
                 }
                 const int ln = level_of(sig, k, lk);
                 chg = live && ln != lo_;
@@ -1240,7 +1281,7 @@ struct Sim {
                         gs &= G_FLAGS;
                     } else if ((gs >> kLtrShift) <= 1u) {
                         gs = (gs & G_FLAGS & ~G_PROMO) | G_DIRTY;  // back to key D
-                        pk2 = pack((int64_t)(w - Pp[idx]) + left, idx);
+                        pk2 = pack((int64_t)(w - Pp()[idx]) + left, idx);
                         chg = true;
                     } else {
                         gs -= 1u << kLtrShift;
@@ -1287,7 +1328,7 @@ struct Sim {
                     if (ad) {  // end-to-end latencies enter the window in batch order
                         uint32_t lat = 0;
                         if (fin) {
-                            const int64_t e2e = t_end - arr[idx_of(pk)];
+                            const int64_t e2e = t_end - arr()[idx_of(pk)];
                             lat = e2e > 0xFFFFFFFFll ? 0xFFFFFFFFu : (uint32_t)e2e;
                         }
                         for (uint64_t m = fm; m; m &= m - 1)
@@ -1337,7 +1378,7 @@ struct Sim {
         lo = INT32_MAX;
         nmoved = 0;
         // time: the r-th iteration starts before the next arrival and `limit`
-        int64_t stop = limit;
+        int room = sat31(limit - t);
         if (next < n_known()) {
             int off = next - pf;
             if (off >= kWave) {
@@ -1345,23 +1386,20 @@ struct Sim {
                 load_pf();
                 off = 0;
             }
-            const int64_t an = rl64(pa, off);
-            stop = an < stop ? an : stop;
+            room = min(room, sat31(rl64(pa, off) - t));
         }
-        const int64_t fixed = (int64_t)base + (int64_t)tok * nb;
+        const Cost cm_ = cost_model();
+        const int64_t fixed = cm_.fixed(nb);
         const int64_t top = sum_ctx + (int64_t)kWave * nb;  // the context of iteration 64
-        if (UNLIKELY(fixed >= (1 << 24) || (top >> 32))) return 0;
-        const uint64_t qt = ctx_quot((uint64_t)(sum_ctx + (int64_t)(lane() + 1) * nb));
+        if (UNLIKELY(((uint64_t)fixed >> 24) || (top >> 32))) return 0;
+        const uint64_t qt = cm_.quot((uint64_t)(sum_ctx + (int64_t)(lane() + 1) * nb));
         if (UNLIKELY((uint32_t)rl((int)(uint32_t)qt, 63) >= (1u << 24))) return 0;
         const int cost = (int)fixed + (int)qt;
         const int tend = scan_add(cost);  // below 64 * 2^25
-        const int64_t room = stop - t;    // > 0
         int r = kWave;
-        if (room <= INT32_MAX) {
-            const uint64_t late = ballot(tend >= (int)room);
-            if (late) r = ffs0(late) + 1;
-        }
-        if (max_iters - iters < r) r = (int)(max_iters - iters);
+        const uint64_t late = ballot(tend >= room);  // (a saturated room is never reached)
+        if (late) r = ffs0(late) + 1;
+        r = min(r, sat31(args()->max_iters - iters));
         // events of the members (and, under LTR+, of the waiting entries)
         const int nch = (L + kWave - 1) >> 6;
         const bool all = EXT && pol == P_LTR;
@@ -1379,7 +1417,7 @@ struct Sim {
                 if constexpr (EXT) {
                     if (phase_signal || cache_signal) {
                         const int ix = min(idx_of(S.k[min(i, L - 1)]), N - 1);
-                        sig -= phase_signal ? Pp[ix] : Hp[ix];
+                        sig -= phase_signal ? Pp()[ix] : Hp()[ix];
                     }
                 }
                 // (signals stay below 2^24: a threshold beyond is never reached)
@@ -1396,7 +1434,7 @@ struct Sim {
         if (r <= 0) return 0;
         // KV: every iteration's new blocks fit (the growth only adds up, so the
         // last one's total decides); halved until they do
-        while (UNLIKELY(U + (int64_t)nb * blocks(r) > Kb)) {
+        while (UNLIKELY(nb * blocks(r) > Kb - U)) {
             int grow = 0;
             for (uint64_t todo = emit_chunks; todo; todo &= todo - 1) {
                 const int i = ffs0(todo) * kWave + lane();
@@ -1404,7 +1442,7 @@ struct Sim {
                 const int kv = skv(q);
                 if (i < L && i <= last && (q.x & G_RES)) grow += blocks(kv + r) - blocks(kv);
             }
-            if ((int64_t)U + wsum(grow) <= Kb) break;
+            if (wsum(grow) <= Kb - U) break;
             r >>= 1;
             if (r == 0) return 0;
         }
@@ -1418,8 +1456,6 @@ struct Sim {
         const int64_t t_end = t + rl(tend, r - 1);
         const uint32_t t32 = (uint32_t)t_end, gap = (uint32_t)rl(cost, r - 1);  // costs never shrink
         int lohole = INT32_MAX, nd = 0, grow = 0, ufree = 0, kfree = 0;
-        steps++;
-        echunks += popc(chunks);
         for (uint64_t todo = chunks; todo; todo &= todo - 1) {
             const int b = ffs0(todo) * kWave;
             const int i = b + lane(), i0 = min(i, L - 1);
@@ -1440,8 +1476,8 @@ struct Sim {
             if (fm) {
                 const int idx = idx_of(S.k[i0]);
                 if (fin) {
-                    tlast[idx] = t_end;
-                    tbo[idx] = gm;
+                    tlast()[idx] = t_end;
+                    tbo()[idx] = gm;
                 }
                 if (lohole == INT32_MAX) lohole = b + ffs0(fm);
                 nd += popc(fm);
@@ -1450,7 +1486,7 @@ struct Sim {
                     if (ad) {
                         uint32_t lat = 0;
                         if (fin) {
-                            const int64_t e2e = t_end - arr[idx];
+                            const int64_t e2e = t_end - arr()[idx];
                             lat = e2e > 0xFFFFFFFFll ? 0xFFFFFFFFu : (uint32_t)e2e;
                         }
                         for (uint64_t m = fm; m; m &= m - 1)
@@ -1465,7 +1501,7 @@ struct Sim {
                 if constexpr (EXT) {
                     if (phase_signal || cache_signal) {
                         const int ix = min(idx_of(S.k[i0]), N - 1);
-                        sig -= phase_signal ? Pp[ix] : Hp[ix];
+                        sig -= phase_signal ? Pp()[ix] : Hp()[ix];
                     }
                 }
                 const bool chg = memb && !fin && k <= (0xffffff >> (ol + 1)) &&
@@ -1502,7 +1538,7 @@ struct Sim {
                         } else if (quota <= r) {  // the quantum ends: back to key D
                             gs = (gs & G_FLAGS & ~G_PROMO) | G_DIRTY;
                             const int idx = idx_of(pk);
-                            S.k[i] = pack((int64_t)(w - Pp[idx]) + left, idx);
+                            S.k[i] = pack((int64_t)(w - Pp()[idx]) + left, idx);
                             chg = true;
                         } else {
                             gs -= (uint32_t)r << kLtrShift;
@@ -1533,11 +1569,11 @@ struct Sim {
         wsync();
         if (pol == P_TRAIL) vm_ok = false;  // eligibility depends on progress
         iters += r;
-        reqiters += (int64_t)r * nb;
-        tokens += (int64_t)r * nb;
+        ev_vol = ev_forced = 0;
+        tally(r * nb, r * nb, 4 + 3 * popc(chunks));
         sum_ctx += (int64_t)r * nb;
         U += wsum(grow);
-        if (U > maxU) maxU = U;
+        maxU = max(maxU, U);
         if (nd) {
             U -= wsum(ufree);
             sum_ctx -= wsum(kfree);
@@ -1581,7 +1617,7 @@ struct Sim {
             if (ext) {
                 y.gs &= ~G_DIRTY;
                 const int xi = nx + mbcnt(xm);
-                if (xi >= kStage) ovf[xi - kStage] = to_rec(y);
+                if (xi >= kStage) ovf()[xi - kStage] = to_rec(y);
             }
             wsync();
             if (xm && nx < kStage) {  // the first kStage extracted stay in registers
@@ -1740,7 +1776,7 @@ struct Sim {
                 for (int b = kStage; b < nx && status == 0; b += kStage) {
                     const int kb = min(nx - b, kStage);
                     R x;
-                    if (lane() < kb) x = from_rec(ovf[b - kStage + lane()]);
+                    if (lane() < kb) x = from_rec(ovf()[b - kStage + lane()]);
                     add_entries(x, kb);
                 }
             }
@@ -1881,6 +1917,7 @@ struct Sim {
     DEV void ada_rekey(int cell) {
         const int64_t *nt = ad->table[cell];
         hbm_fence();
+        Rec *const spill = this->spill();
         uint64_t mn = ~0ull;
         for (int b = 0; b < spill_n; b += kWave) {
             const int i = b + lane();
@@ -1918,7 +1955,7 @@ struct Sim {
             for (int b = kStage; b < nx && status == 0; b += kStage) {
                 const int kb = min(nx - b, kStage);
                 R x;
-                if (lane() < kb) x = from_rec(ovf[b - kStage + lane()]);
+                if (lane() < kb) x = from_rec(ovf()[b - kStage + lane()]);
                 add_entries(x, kb);
             }
         }
@@ -1929,7 +1966,7 @@ struct Sim {
     // The batch just formed respects the sequence cap, the token budget and
     // the KV budget, and every member computes at least one token.
     DEV void check_batch() {
-        if (cnt < 1 || cnt > M || used < cnt || used > T || U < 0 || U > Kb) fail(S_ESTATE);
+        if (cnt < 1 || cnt > M || used < cnt || used > args()->T || U < 0 || U > Kb) fail(S_ESTATE);
     }
 
     // The state between iterations: the list's residents, waiting entries
@@ -1941,7 +1978,7 @@ struct Sim {
     // spill holds waiting entries only, its minimum is exact; and every
     // request taken so far is done, on chip or spilled.
     DEV void check_state() {
-        bool bad = U < 0 || U > Kb || L < 0 || L > cap_now() || spill_n < 0 || spill_n > scap;
+        bool bad = U < 0 || U > Kb || L < 0 || L > cap_now() || spill_n < 0 || spill_n > scap();
         int nres = 0, nwait = 0, nhole = 0, blk = 0;
         uint64_t pmax = 0;  // 1 + the largest key of the live entries so far (0: none)
         for (int b = 0; b < L && !bad; b += kWave) {
@@ -1985,7 +2022,7 @@ struct Sim {
             for (int b = 0; b < spill_n; b += kWave) {
                 const int i = b + lane();
                 if (i < spill_n) {
-                    const Rec x = spill[i];
+                    const Rec x = spill()[i];
                     if (x.pk < mn) mn = x.pk;
                     e = e || (x.gs & (G_RES | G_DONE | G_INB | G_EVI | G_MARK | G_DIRTY)) != 0 ||
                         x.kv != 0 || x.left < 1 || idx_of(x.pk) >= N;
@@ -2011,10 +2048,10 @@ struct Sim {
             if (full && at >= 0) {
                 last = at;
                 const uint64_t pk = uniu(S.k[at]);
-                bar = pk < bar ? pk : bar;
+                bar = sgpr64(pk < bar ? pk : bar);
             }
         }
-        return next == next0 || (bar != ~0ull && arr_min_pk > bar);
+        return next == next0 || (bar != ~0ull && !ballot(arr_pk <= bar));
     }
 
     // Sarathi: the first live entry of the list is a resident, so no waiting
@@ -2035,7 +2072,7 @@ struct Sim {
     // One iteration, or a run of repeated ones; then the list's maintenance
     // and the arrivals. `limit`: see streak.
     DEV void step(int64_t limit) {
-        pin();
+        sum_ctx = (int64_t)sgpr64((uint64_t)sum_ctx);
         const int c0 = completed, next0 = next, sp0 = n_spilled;
         int lo_mod = INT32_MAX;
         // Does the next iteration repeat this one's batch? `again`: every
@@ -2050,7 +2087,6 @@ struct Sim {
                     if (status) return;
                 }
             }
-            const int64_t ev0 = ev_vol + ev_forced;
             formation();
             if (status) return;
             if (cnt == 0) {
@@ -2063,25 +2099,23 @@ struct Sim {
             }
             whole = cnt == nR;
             nb = cnt;
-            stays = ev_vol + ev_forced == ev0 && !emit_all && used < T;
-            if (U > maxU) maxU = U;
-            const int64_t dt =
-                (int64_t)base + (int64_t)tok * used + (int64_t)ctx_quot((uint64_t)sum_ctx);
+            stays = ev_vol + ev_forced == 0 && !emit_all && used < args()->T;
+            maxU = max(maxU, U);
+            const Cost cost = cost_model();
+            const int64_t dt = cost.fixed(used) + (int64_t)cost.quot((uint64_t)sum_ctx);
             const int64_t t_end = t + dt;
             lo_mod = emission(t_end);
             again = all_emit;
             t = t_end;
             iters++;
-            steps++;
-            reqiters += cnt;
-            tokens += used;
-            if (iters > max_iters) {
+            tally(cnt, used, 4 + 5 * fpass + 3 * n_chunks);
+            if (less64(args()->max_iters, iters)) {
                 fail(S_ELIVELOCK);
                 return;
             }
         }
         if constexpr (CL) last_done = completed - c0;
-        arr_min_pk = ~0ull;
+        arr_pk = ~0ull;
         const bool edited = maintenance(lo_mod);
         // A whole batch repeats (as far as the KV budget allows: see streak)
         // if nothing waits. With requests waiting, or residents left out of
@@ -2146,7 +2180,7 @@ struct Sim {
                     off = 0;
                 }
                 const int64_t an = rl64(pa, off);
-                idle += an - t;
+                if (lane() == 0) S.ty[TY_IDLE] += (uint64_t)(an - t);
                 t = an;
                 take_arrivals();
                 continue;
@@ -2163,7 +2197,7 @@ struct Sim {
     DEV void run_until(int64_t limit) {
         if (status) return;
         const int next0 = next, sp0 = n_spilled;
-        arr_min_pk = ~0ull;
+        arr_pk = ~0ull;
         take_arrivals();  // the router may have dispatched since the last call
         if (rep && next != next0) rep = n_spilled == sp0 && arrivals_keep(next0, true);
         for (;;) {
@@ -2186,12 +2220,12 @@ struct Sim {
                     off = 0;
                 }
                 const int64_t an = rl64(pa, off);  // <= limit: dispatched requests have arrived
-                idle += an - t;
+                if (lane() == 0) S.ty[TY_IDLE] += (uint64_t)(an - t);
                 t = an;
                 take_arrivals();
                 continue;
             }
-            if (t >= limit) return;
+            if (!less64(t, limit)) return;
             step(limit);
         }
     }
@@ -2204,12 +2238,12 @@ struct Sim {
     // CL: the router sends global request j to this replica.
     DEV void dispatch(int j) {
         if (lane() == 0) {
-            __hip_atomic_store(&jl[Nk], j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&jl()[Nk], j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             A.assign[(size_t)inst * (size_t)N + (size_t)j] = wv;
         }
         // the prefetch window [pf, pf + 64) takes the new entry now, as a
         // reload from the list would (pf <= next <= Nk)
-        if (lane() == Nk - pf) pidx = j, pa = arr[j], pP = Pp[j], pD = Dp[j];
+        if (lane() == Nk - pf) pidx = j, pa = arr()[j], pP = Pp()[j], pD = Dp()[j];
         Nk++;
         hbm_fence();
     }
@@ -2218,6 +2252,8 @@ struct Sim {
     // (HBM, and in `cn` for the instance's totals) and status (`st`).
     DEV void finish_cl(int64_t *cn, int32_t *st) {
         hbm_fence();
+        const int64_t *const arr = this->arr(), *const tfirst = this->tfirst(),
+                      *const tlast = this->tlast();
         if (status == 0 && completed != Nk) fail(S_ESTATE);
         if (status == 0) {
             const size_t ioff = (size_t)inst * (size_t)N;
@@ -2225,7 +2261,7 @@ struct Sim {
             for (int b = 0; b < Nk; b += kWave) {
                 const int kk = b + lane();
                 if (kk < Nk) {
-                    const int i = __hip_atomic_load(&jl[kk], __ATOMIC_RELAXED,
+                    const int i = __hip_atomic_load(&jl()[kk], __ATOMIC_RELAXED,
                                                     __HIP_MEMORY_SCOPE_AGENT);
                     const int64_t a = arr[i];
                     const int64_t f = tfirst[i] - a, l = tlast[i] - a;
@@ -2237,7 +2273,9 @@ struct Sim {
             if (ballot(bad)) fail(S_EOVERFLOW);
         }
         if (lane() == 0) {
-            const int64_t v[8] = {iters, reqiters, tokens, ev_vol, ev_forced, t, maxU, idle};
+            const int64_t v[8] = {iters, (int64_t)S.ty[TY_REQITERS], (int64_t)S.ty[TY_TOKENS],
+                                  (int64_t)S.ty[TY_EVVOL], (int64_t)S.ty[TY_EVFORCED], t,
+                                  (int64_t)maxU, (int64_t)S.ty[TY_IDLE]};
             const size_t slot = (size_t)inst * (size_t)A.replicas + (size_t)wv;
             int64_t *rc = A.rcounters + slot * 8;
             for (int q = 0; q < 8; q++) rc[q] = v[q], cn[q] = v[q];
@@ -2249,6 +2287,8 @@ struct Sim {
 
     DEV void finish() {
         hbm_fence();
+        const int64_t *const arr = this->arr(), *const tfirst = this->tfirst(),
+                      *const tlast = this->tlast();
         if (status == 0 && completed != N) fail(S_ESTATE);
         if (status == 0) {
             const size_t ioff = (size_t)inst * (size_t)N;
@@ -2267,17 +2307,16 @@ struct Sim {
         }
         if (lane() == 0) {
             int64_t *cn = A.counters + (size_t)inst * 8;
-            cn[0] = iters, cn[1] = reqiters, cn[2] = tokens, cn[3] = ev_vol;
-            cn[4] = ev_forced, cn[5] = t, cn[6] = maxU, cn[7] = idle;
+            cn[0] = iters, cn[1] = (int64_t)S.ty[TY_REQITERS], cn[2] = (int64_t)S.ty[TY_TOKENS];
+            cn[3] = (int64_t)S.ty[TY_EVVOL], cn[4] = (int64_t)S.ty[TY_EVFORCED], cn[5] = t;
+            cn[6] = maxU, cn[7] = (int64_t)S.ty[TY_IDLE];
             // the next launch's order key: the loop steps this wave ran,
             // weighted by their measured cost (a step's fixed work 4, a
             // formation pass over up to 64 candidates 5, an emission chunk
             // 3), and far below them the iterations themselves, which a run
             // of repeated ones takes at once. Unlike wall-clock time it does
             // not depend on the slot the instance ran in.
-            if (A.work)
-                A.work[inst] = 4 * iters + 64 * (4 * (int64_t)steps + 5 * (int64_t)fpass +
-                                                 3 * (int64_t)echunks);
+            if (A.work) A.work[inst] = 4 * iters + 64 * (int64_t)S.ty[TY_WORK];
             if constexpr (EXT) {  // (zero from tas_create for the other build)
                 A.gamma_out[inst] = ad ? S.as->gamma : 0.0;
                 A.switch_out[inst] = ad ? S.as->switches : 0;
@@ -2289,7 +2328,7 @@ struct Sim {
 
 template <int BSH, bool EXT, bool CP>
 DEV void run_instance(const SimArgs &a, const DevSetting &st, int inst, unsigned char *smem) {
-    Sim<BSH, EXT, false, CP> s(a, st, inst, smem);
+    Sim<BSH, EXT, false, CP> s(a, st, inst, smem + kTallyBytes, (uint64_t *)smem);
     s.run();
 }
 
@@ -2311,7 +2350,8 @@ template <int BSH>
 DEV void run_cluster(const SimArgs &a, const DevSetting &st, int inst, unsigned char *smem) {
     JsqLds *J = (JsqLds *)smem;
     const int R = a.replicas, w = (int)(threadIdx.x >> 6), N = a.n_req;
-    Sim<BSH, true, true> s(a, st, inst, smem + kJsqLdsBytes + (size_t)w * (size_t)a.wave_lds, w);
+    Sim<BSH, true, true> s(a, st, inst, smem + kJsqLdsBytes + (size_t)w * (size_t)a.wave_lds,
+                           (uint64_t *)J->cn[w], w);
     const int64_t *arr = a.arrival + (size_t)st.trace * (size_t)N;
     s.load_pf();  // nothing dispatched yet: an empty window, kept current by dispatch
     for (int j = 0;; j++) {  // j = N: run what was dispatched to the end
