@@ -341,7 +341,9 @@ struct Sim {
     int wv, Nk, pidx, last_done;
     // per-iteration formation results
     int cnt, used;
-    int64_t sum_ctx;
+    int64_t sum_ctx;  // KV tokens of the batch, this iteration's included
+    int64_t kv_res;   // KV tokens of all residents
+    int evl;  // per lane: iterations to the next event of the batch's members (see streak)
     uint64_t emit_chunks;  // 64-entry chunks holding batch members or evictions
     bool emit_all;         // ranks moved during formation: visit every chunk
     // Repeated batch: the next iteration's formation would select the same
@@ -449,7 +451,8 @@ struct Sim {
         iters = 0, maxU = 0;
         ev_vol = ev_forced = fpass = 0;
         cnt = used = 0;
-        sum_ctx = 0;
+        sum_ctx = kv_res = 0;
+        evl = INT32_MAX;
         emit_chunks = 0;
         emit_all = false;
         rep = all_emit = false;
@@ -566,11 +569,29 @@ struct Sim {
         c.base = a->base, c.tok = a->tok, c.div = a->div, c.div_magic = a->div_magic;
         return c;
     }
+    // The signal at which level `lvl` ends, k 2^(lvl+1) (signals stay below
+    // 2^24: INT32_MAX for a threshold beyond, and above the last level).
+    DEV int next_level(int lvl) const {
+        return k <= (0xffffff >> (lvl + 1)) ? k << (lvl + 1) : INT32_MAX;
+    }
     DEV int blocks(int x) const {
         if constexpr (BSH >= 0) {
             return (x + (1 << BSH) - 1) >> BSH;
         } else {
             return (x + bs - 1) / bs;
+        }
+    }
+
+    // New KV blocks of the members (one per lane; kv tokens each) for r more
+    // tokens each, over the wave: with power-of-two blocks r / bs each, and
+    // one more where r mod bs exceeds what is free in the last block.
+    DEV int growth(bool memb, int kv, int r) const {
+        if constexpr (BSH >= 0) {
+            const int m = (1 << BSH) - 1;
+            const uint64_t all = ballot(memb), more = ballot(memb && ((-kv) & m) < (r & m));
+            return popc(all) * (r >> BSH) + popc(more);
+        } else {
+            return wsum(memb ? blocks(kv + r) - blocks(kv) : 0);
         }
     }
 
@@ -971,6 +992,7 @@ struct Sim {
             stxkv(v, (g & ~G_RES) | G_EVI | (pol == P_SRPT || pol == P_TRAIL ? G_DIRTY : 0u), wv_, 0);
         wsync();
         U -= blocks(kvv);
+        kv_res -= kvv;
         nW++;
         nR--;
         emit_chunks |= 1ull << (v >> 6);
@@ -979,7 +1001,7 @@ struct Sim {
 
     // Admission of candidate q with n tokens: its KV advances now (emission
     // finds the tokens scheduled this iteration already counted).
-    DEV void admit_one(int q, uint32_t g, int n, int du, int kvv, int wq) {
+    DEV void admit_one(int q, uint32_t g, int n, int du, int kvv, int wq, int64_t &ctx_one) {
         const bool res = (g & G_RES) != 0;
         if (lane() == 0) {
             uint32_t g2 = g | G_INB;
@@ -990,7 +1012,7 @@ struct Sim {
         cnt++;
         used += n;
         U += du;
-        sum_ctx += kvv + n;
+        ctx_one += kvv + n;
         if (!res) {
             nW--, nR++;
             vm_set(q, true);
@@ -1002,11 +1024,11 @@ struct Sim {
     // counts residents at ranks > q.
     // (g, n, du, kvv, wq: its flag word, chunk size, KV blocks, KV tokens and w)
     DEV void slow_path(int q, uint32_t g, int n, int du, int kvv, int wq, bool &closed,
-                       int &r_ahead) {
+                       int &r_ahead, int64_t &ctx_one) {
         const bool res = (g & G_RES) != 0;
         for (int it = 0; it <= L + 1; it++) {
             if (U + du <= Kb) {
-                admit_one(q, g, n, du, kvv, wq);
+                admit_one(q, g, n, du, kvv, wq, ctx_one);
                 return;
             }
             int v = find_victim(q, true);
@@ -1057,33 +1079,42 @@ struct Sim {
         emit_all = true;
     }
 
+    // Bound by its dependent chain (loads, ballots, scans), so a chunk whose
+    // candidates all fit skips the prefix sums: at most one of them computes
+    // more than one token nearly always, and ballots then give the totals.
+    // The batch's context is the residents' (kept up to date as they change)
+    // unless some are left out.
     DEV void formation() {
+        // a formation that closed admissions is followed by others that do:
+        // no use in adding up the candidates before the closing one
+        const bool tight = close_pk != ~0ull;
         close_pk = ~0ull;
         ev_vol = ev_forced = fpass = 0;
         cnt = 0, used = 0;
-        sum_ctx = 0;
         emit_chunks = 0;
         emit_all = false;
         bool closed = false;
         int r_ahead = nR;  // residents at ranks >= p
         int p = 0;
+        uint64_t vctx = 0;    // per lane: KV tokens of the members admitted by chunk,
+        int64_t ctx_one = 0;  // and of those admitted one by one
         int bstar = spill_n > 0 ? lower_bound(spill_min) : INT32_MAX;
         // the next chunk's records, loaded while this one is processed; valid
         // while formation walks whole chunks without touching the list
         const int lim = lcap + kStage;
-        const int T = args()->T, c = args()->c;
+        KArgs *const ka = args();
+        const int T = ka->T, c = ka->c;
+        const uint32_t max_pass = (uint32_t)lim + (uint32_t)ka->spill_cap + 2u;
         uint4 nx = make_uint4(0u, 0u, 0u, 0u);
         bool have_nx = false;
         // every pass advances p or refills from the spill, so the walk ends
         // within L + spill_cap passes; a walk that does not is a broken state
-        for (int pass = 0;; pass++) {
-            fpass++;
-            if (UNLIKELY(pass > lcap + kStage + scap() + 2)) {
-                fail(S_ESTATE);
-                return;
-            }
-            if (cnt >= M || used >= T || (closed && r_ahead <= 0)) break;
+        for (;;) {
             if (UNLIKELY(!closed && p >= bstar)) {  // bstar <= L: spilled entries come next
+                if (UNLIKELY((uint32_t)++fpass > max_pass)) {
+                    fail(S_ESTATE);
+                    return;
+                }
                 mid_refill(p);
                 if (status) return;
                 bstar = spill_n > 0 ? lower_bound(spill_min) : INT32_MAX;
@@ -1091,6 +1122,10 @@ struct Sim {
                 continue;
             }
             if (p >= L) break;
+            if (UNLIKELY((uint32_t)++fpass > max_pass)) {
+                fail(S_ESTATE);
+                return;
+            }
             const int end = closed ? L : min(L, bstar);
             const int r = p + lane();
             const bool valid = r < end;
@@ -1103,41 +1138,56 @@ struct Sim {
             const int kvv = skv(qr);
             const bool res = (g & G_RES) != 0;
             const bool cand = valid && !(g & (G_EVI | G_DONE)) && (res || !closed);
-            // one round of scans: the candidates admitted from this chunk
-            // are a prefix of its candidates, and only the last of them can
-            // be clipped by the token budget
             const int m = cand ? min(w - kvv, c) : 0;
-            const int kvc = cand ? kvv : 0;
-            const int dfull = cand ? blocks(kvv + m) - blocks(kvv) : 0;
-            const int mi = scan_add(m);
-            const int dfi = scan_add(dfull);
-            const int kvi = scan_add(kvc);
-            const uint64_t cm = ballot(cand);
-            const int cb = cnt + mbcnt(cm);
-            const int ub = used + mi - m;
-            const bool adm = cand && cb < M && ub < T;
-            const int n = adm ? min(m, T - ub) : 0;
-            const int du = adm ? blocks(kvv + n) - blocks(kvv) : 0;
-            const int dui = dfi - dfull + du;
-            const bool fit = U + dui <= Kb;
-            const uint64_t bad = ballot(adm && !fit);
-            const uint64_t am = ballot(adm);
-            const uint64_t okm = bad ? (am & ((1ull << ffs0(bad)) - 1ull)) : am;
+            const int d = cand ? blocks(kvv + m) - blocks(kvv) : 0;
+            const uint64_t cm = ballot(cand), resm = ballot(res);
+            int mt = 0, dt = 0;  // tokens and blocks of the lanes admitted
+            bool all = closed || !tight;
+            if (all) {  // do all candidates fit?
+                const uint64_t big = ballot(m > 1);
+                mt = popc(cm), dt = popc(ballot(d > 0));
+                if (big & (big - 1)) {
+                    mt = wsum(m), dt = wsum(d);
+                } else if (big) {
+                    const int l = ffs0(big), db = rl(d, l);
+                    mt += rl(m, l) - 1;
+                    dt += db > 0 ? db - 1 : 0;
+                }
+                all = cnt + popc(cm) <= M && mt <= T - used && dt <= Kb - U;
+            }
+            uint64_t okm = cm, bad = 0;
+            int n = m, du = d;
+            if (!all) {
+                // the candidates admitted from this chunk are a prefix of
+                // its candidates, and only the last of them can be clipped
+                // by the token budget
+                const int ub = used + scan_add(m) - m;
+                const int dfi = scan_add(d);
+                const bool adm = cand && cnt + mbcnt(cm) < M && ub < T;
+                n = adm ? min(m, T - ub) : 0;
+                du = adm ? blocks(kvv + n) - blocks(kvv) : 0;
+                const int dui = dfi - d + du;
+                bad = ballot(adm && U + dui > Kb);
+                const uint64_t am = ballot(adm);
+                okm = bad ? (am & ((1ull << ffs0(bad)) - 1ull)) : am;
+                if (okm) {
+                    const int last_ = fls0(okm);
+                    mt = rl(ub + n, last_) - used, dt = rl(dui, last_);
+                }
+            }
             const bool ok = ((okm >> lane()) & 1ull) != 0;
             if (ok) {  // admitted: the KV advances by this iteration's chunk now
                 uint32_t g2 = g | G_INB;
                 if (!res) g2 = (g2 & ~G_GUARD) | G_RES | ((g >> G_LVL_SHIFT) & 31u);
                 stxkv(r, g2, w, kvv + n);
+                vctx += (uint32_t)(kvv + n);
             }
             if (okm) {
-                const int last = fls0(okm);
-                const int used_new = rl(ub + n, last);
-                const uint64_t nm = ballot(ok && !res);
+                const uint64_t nm = okm & ~resm;
                 const int nadm_w = popc(nm);
                 cnt += popc(okm);
-                sum_ctx += rl(kvi, last) + (used_new - used);
-                used = used_new;
-                U += rl(dui, last);
+                used += mt;
+                U += dt;
                 nW -= nadm_w;
                 nR += nadm_w;
                 if (pol == P_TRAIL && nadm_w) vm_ok = false;  // eligibility depends on progress
@@ -1149,9 +1199,8 @@ struct Sim {
                     if (lane() == c0) vm_res |= lo, vm_ev |= ev_too ? lo : 0ull;
                     if (lane() == c0 + 1) vm_res |= hi, vm_ev |= ev_too ? hi : 0ull;
                 }
-                emit_chunks |= (1ull << ((p + ffs0(okm)) >> 6)) | (1ull << ((p + last) >> 6));
+                emit_chunks |= (1ull << ((p + ffs0(okm)) >> 6)) | (1ull << ((p + fls0(okm)) >> 6));
             }
-            const uint64_t resm = ballot(valid && res);
             wsync();
             if (bad) {
                 const int ql = ffs0(bad);
@@ -1159,7 +1208,7 @@ struct Sim {
                 // waiting entries admitted in this chunk sit below q
                 r_ahead -= popc(resm & (ql == 63 ? ~0ull : ((2ull << ql) - 1ull)));
                 slow_path(p + ql, (uint32_t)rl((int)g, ql), rl(n, ql), rl(du, ql), rl(kvv, ql),
-                          rl(w, ql), closed, r_ahead);
+                          rl(w, ql), closed, r_ahead, ctx_one);
                 if (status) return;
                 p = p + ql + 1;
                 have_nx = false;
@@ -1169,7 +1218,14 @@ struct Sim {
                 have_nx = p2 == p + kWave;
                 p = p2;
             }
+            if (cnt >= M || used >= T || (closed && r_ahead <= 0)) break;
         }
+        kv_res += used;
+        sum_ctx = kv_res;
+        if (cnt != nR)  // residents outside the batch
+            sum_ctx = ctx_one + wsum((int)(vctx & 0xffff)) +
+                      ((int64_t)wsum((int)(vctx >> 16) & 0xffff) << 16) +
+                      ((int64_t)wsum((int)(vctx >> 32)) << 32);
     }
 
     // ---------------------------------------------------------- execute
@@ -1178,6 +1234,7 @@ struct Sim {
     DEV int emission(int64_t t_end) {
         int lo = INT32_MAX, lohole = INT32_MAX, nd = 0, ufree = 0, kfree = 0, nmv = 0;
         nmoved = 0, n_chunks = 0;
+        evl = INT32_MAX;
         bool bad_idx = false;
         uint64_t noemit = 0;  // batch members that emitted no token
         const uint32_t t32 = (uint32_t)t_end;
@@ -1243,6 +1300,7 @@ struct Sim {
             const bool live = emit && !fin;  // emitted and has tokens left
             bool chg = false;
             uint64_t pk2 = pk;
+            int ev = left;  // iterations to this member's next event
             if (pol == P_LAS) {
                 // the attained service grew by one token
                 chg = live;
@@ -1254,14 +1312,21 @@ struct Sim {
             } else if (pol == P_BOOST) {
                 const int lo_ = (int)((gs >> G_LVL_SHIFT) & 31u);
                 int sig = w;  // P + dec
+                int ln = lo_;
                 if constexpr (EXT) {
                     // every lane reads: keep non-member lanes in bounds
                     const int ix = min(idx, N - 1);
                     if (phase_signal) sig = w - Pp()[ix];  // dec >= 1 after this token
                     if (cache_signal) sig = w - Hp()[ix];  // P - h + dec
+                    if (phase_signal) ln = level_of(sig, k, lk);  // may fall at the first token
                 }
-                const int ln = level_of(sig, k, lk);
+                // the signal grows by one a token: the level follows when it
+                // reaches the next threshold
+                int thr = next_level(ln);
+                const bool up = sig >= thr;
+                ln += up ? 1 : 0;
                 chg = live && ln != lo_;
+                ev = min(ev, (thr << (up ? 1 : 0)) - sig);
                 if (chg) {  // a level crossing (rare): re-key by the table step
                     pk2 = pack(key_of(pk) + S.bt[lo_] - S.bt[ln], idx);
                     gs = (gs & ~G_LVL) | ((uint32_t)ln << G_LVL_SHIFT);
@@ -1286,6 +1351,7 @@ struct Sim {
                     } else {
                         gs -= 1u << kLtrShift;
                     }
+                    if (gs & G_PROMO) ev = min(ev, max((int)(gs >> kLtrShift), 1));
                 }
             }
             // SRPT's and TRAIL's re-keyed entries carry no re-insertion mark:
@@ -1293,9 +1359,10 @@ struct Sim {
             const bool dirty = chg && pol != P_SRPT && pol != P_TRAIL;
             gs |= dirty ? G_DIRTY : 0u;
             const bool mute = memb && !emit;
+            if (live) evl = min(evl, ev);
             if (memb || evi) {
                 stq(r, gs, w, kv, left);
-                S.k[r] = pk2;
+                if (chg) S.k[r] = pk2;
                 S.tg[r] = make_uint2(emit ? t32 : tg.x, gm);
             }
             if constexpr (EXT) {
@@ -1310,6 +1377,8 @@ struct Sim {
                         pk2 = pack(iters + 1 - kPromotedOff, idx);
                         S.k[r] = pk2;
                         chg = true;
+                    } else {
+                        evl = min(evl, ltr_s - (int)cnt);
                     }
                     stx(r, gx);
                 }
@@ -1344,8 +1413,9 @@ struct Sim {
         all_emit = noemit == 0;
         nmoved = nmv;
         if (nd) {
+            const int kf = wsum(kfree);
             U -= wsum(ufree);
-            sum_ctx -= wsum(kfree);
+            sum_ctx -= kf, kv_res -= kf;
             completed += nd;
             nR -= nd;
             n_holes += nd;
@@ -1400,37 +1470,7 @@ struct Sim {
         const uint64_t late = ballot(tend >= room);  // (a saturated room is never reached)
         if (late) r = ffs0(late) + 1;
         r = min(r, sat31(args()->max_iters - iters));
-        // events of the members (and, under LTR+, of the waiting entries)
-        const int nch = (L + kWave - 1) >> 6;
-        const bool all = EXT && pol == P_LTR;
-        const uint64_t chunks = all ? (nch >= 64 ? ~0ull : ((1ull << nch) - 1ull)) : emit_chunks;
-        int ev = r;
-        for (uint64_t todo = chunks; todo; todo &= todo - 1) {
-            const int i = ffs0(todo) * kWave + lane();
-            const uint4 q = ldq(min(i, L - 1));
-            const uint32_t g = i < L ? q.x : 0u;
-            const bool memb = (g & G_RES) != 0 && i <= last;
-            int e = sleft(q);
-            if (pol == P_BOOST) {  // tokens to the next level's threshold k 2^(level+1)
-                const int up = (int)((g >> G_LVL_SHIFT) & 31u) + 1;
-                int sig = sw(q);
-                if constexpr (EXT) {
-                    if (phase_signal || cache_signal) {
-                        const int ix = min(idx_of(S.k[min(i, L - 1)]), N - 1);
-                        sig -= phase_signal ? Pp()[ix] : Hp()[ix];
-                    }
-                }
-                // (signals stay below 2^24: a threshold beyond is never reached)
-                if (k <= (0xffffff >> up)) e = min(e, (k << up) - sig);
-            }
-            if constexpr (EXT) {
-                if (pol == P_LTR && (g & G_PROMO)) e = min(e, max((int)(g >> kLtrShift), 1));
-                if (pol == P_LTR && i < L && !memb && !(g & (G_DONE | G_PROMO)))
-                    ev = min(ev, ltr_s - (int)(g >> kLtrShift));
-            }
-            if (memb) ev = min(ev, e);
-        }
-        r = wmin(ev);
+        r = min(r, wmin(evl));
         if (r <= 0) return 0;
         // KV: every iteration's new blocks fit (the growth only adds up, so the
         // last one's total decides); halved until they do
@@ -1439,10 +1479,9 @@ struct Sim {
             for (uint64_t todo = emit_chunks; todo; todo &= todo - 1) {
                 const int i = ffs0(todo) * kWave + lane();
                 const uint4 q = ldq(min(i, L - 1));
-                const int kv = skv(q);
-                if (i < L && i <= last && (q.x & G_RES)) grow += blocks(kv + r) - blocks(kv);
+                grow += growth(i < L && i <= last && (q.x & G_RES), skv(q), r);
             }
-            if (wsum(grow) <= Kb - U) break;
+            if (grow <= Kb - U) break;
             r >>= 1;
             if (r == 0) return 0;
         }
@@ -1456,6 +1495,11 @@ struct Sim {
         const int64_t t_end = t + rl(tend, r - 1);
         const uint32_t t32 = (uint32_t)t_end, gap = (uint32_t)rl(cost, r - 1);  // costs never shrink
         int lohole = INT32_MAX, nd = 0, grow = 0, ufree = 0, kfree = 0;
+        // LTR+ counts every candidate's starvation: visit every chunk
+        const int nch = (L + kWave - 1) >> 6;
+        const uint64_t chunks =
+            EXT && pol == P_LTR ? (nch >= 64 ? ~0ull : ((1ull << nch) - 1ull)) : emit_chunks;
+        evl = INT32_MAX;
         for (uint64_t todo = chunks; todo; todo &= todo - 1) {
             const int b = ffs0(todo) * kWave;
             const int i = b + lane(), i0 = min(i, L - 1);
@@ -1465,8 +1509,9 @@ struct Sim {
             const bool memb = (g & G_RES) != 0 && i <= last;
             const int w = sw(q) + r, left = sleft(q) - r;
             int kv = skv(q);
-            grow += memb ? blocks(kv + r) - blocks(kv) : 0;
+            grow += growth(memb, kv, r);
             kv += r;
+            int ev = left;
             const bool fin = memb && left == 0;
             ufree += fin ? blocks(kv) : 0;
             kfree += fin ? kv : 0;
@@ -1504,15 +1549,15 @@ struct Sim {
                         sig -= phase_signal ? Pp()[ix] : Hp()[ix];
                     }
                 }
-                const bool chg = memb && !fin && k <= (0xffffff >> (ol + 1)) &&
-                                 sig >= (k << (ol + 1));
+                const int thr = next_level(ol);
+                const bool chg = memb && !fin && sig >= thr;
+                ev = min(ev, (thr << (chg ? 1 : 0)) - sig);
                 cm = ballot(chg);
                 if (cm) {
                     const uint64_t pk = S.k[i0];
                     if (chg) {
-                        const int nl = level_of(sig, k, lk);
-                        S.k[i] = pack(key_of(pk) + S.bt[ol] - S.bt[nl], idx_of(pk));
-                        gs = (gs & ~G_LVL) | ((uint32_t)nl << G_LVL_SHIFT) | G_DIRTY;
+                        S.k[i] = pack(key_of(pk) + S.bt[ol] - S.bt[ol + 1], idx_of(pk));
+                        gs = (gs & ~G_LVL) | ((uint32_t)(ol + 1) << G_LVL_SHIFT) | G_DIRTY;
                     }
                 }
             } else if (pol == P_SRPT || pol == P_TRAIL || pol == P_LAS) {
@@ -1543,6 +1588,7 @@ struct Sim {
                         } else {
                             gs -= (uint32_t)r << kLtrShift;
                         }
+                        if (gs & G_PROMO) ev = min(ev, max((int)(gs >> kLtrShift), 1));
                     } else if (i < L && !memb && !(g & (G_DONE | G_PROMO))) {
                         const uint32_t c2 = (g >> kLtrShift) + (uint32_t)r;
                         uint32_t gx = (g & G_FLAGS) | (c2 << kLtrShift);
@@ -1551,6 +1597,8 @@ struct Sim {
                                  ((uint32_t)ltr_q << kLtrShift);
                             S.k[i] = pack(iters + r - kPromotedOff, idx_of(pk));
                             chg = true;
+                        } else {
+                            evl = min(evl, ltr_s - (int)c2);
                         }
                         stx(i, gx);
                     }
@@ -1560,6 +1608,7 @@ struct Sim {
             if (memb) {
                 stq(i, gs, w, fin ? 0 : kv, left);
                 S.tg[i] = make_uint2(t32, gm);
+                if (!fin) evl = min(evl, ev);
             }
             if (cm) {
                 nmoved += popc(cm);
@@ -1571,12 +1620,13 @@ struct Sim {
         iters += r;
         ev_vol = ev_forced = 0;
         tally(r * nb, r * nb, 4 + 3 * popc(chunks));
-        sum_ctx += (int64_t)r * nb;
-        U += wsum(grow);
+        sum_ctx += r * nb, kv_res += r * nb;
+        U += grow;
         maxU = max(maxU, U);
         if (nd) {
+            const int kf = wsum(kfree);
             U -= wsum(ufree);
-            sum_ctx -= wsum(kfree);
+            sum_ctx -= kf, kv_res -= kf;
             completed += nd;
             nR -= nd;
             n_holes += nd;
@@ -1971,7 +2021,7 @@ struct Sim {
 
     // The state between iterations: the list's residents, waiting entries
     // and holes match their counts; the KV in use is the residents' blocks,
-    // within the budget; the keys of the entries other than holes ascend
+    // within the budget, and their tokens the running sum; the keys of the entries other than holes ascend
     // strictly; holes lie at or after lo_hole; no mark of an iteration (in
     // the batch, evicted, selected for spilling, key moved) survives it; an
     // entry's KV lies within its signal and a waiting entry holds none; the
@@ -1980,6 +2030,7 @@ struct Sim {
     DEV void check_state() {
         bool bad = U < 0 || U > Kb || L < 0 || L > cap_now() || spill_n < 0 || spill_n > scap();
         int nres = 0, nwait = 0, nhole = 0, blk = 0;
+        uint32_t kvs = 0;
         uint64_t pmax = 0;  // 1 + the largest key of the live entries so far (0: none)
         for (int b = 0; b < L && !bad; b += kWave) {
             const int r = b + lane();
@@ -1997,6 +2048,7 @@ struct Sim {
             nwait += wt ? 1 : 0;
             nhole += done ? 1 : 0;
             blk += rs ? blocks(kv) : 0;
+            kvs += rs ? (uint32_t)kv : 0u;
             const uint64_t inc = scan_maxu(live ? pk + 1 : 0ull);
             uint64_t exc = prev_lane_u64(inc, 0ull);
             if (pmax > exc) exc = pmax;
@@ -2013,6 +2065,7 @@ struct Sim {
         if (!bad) {
             nres = wsum(nres), nwait = wsum(nwait), nhole = wsum(nhole), blk = wsum(blk);
             bad = nres != nR || nwait != nW || nhole != n_holes || blk != U ||
+                  (uint32_t)wsum((int)kvs) != (uint32_t)kv_res ||
                   completed + nR + nW + spill_n != next;
         }
         if (!bad && spill_n > 0) {
@@ -2041,6 +2094,9 @@ struct Sim {
     // the members again where ranks may have moved (`moved`).
     DEV bool arrivals_keep(int next0, bool moved) {
         const bool full = nb == M;
+        if constexpr (EXT) {
+            if (pol == P_LTR && next != next0) evl = min(evl, ltr_s);  // they start to starve
+        }
         last = INT32_MAX;
         uint64_t bar = close_pk;
         if (moved || full) {
