@@ -318,9 +318,11 @@ struct Sim {
     const SimArgs &A;
     Lds S;
     // instance constants (memguard and delta are zero unless pol is BOOST)
-    int inst, trace, N, M, Kb, bs, pol, k, lk, memguard, lcap;
+    int inst, trace, N, M, T, c, Kb, bs, base, tok, div, pol, k, lk, memguard, lcap;
     int ltr_s, ltr_q;  // LTR+: starvation threshold and quantum (iterations)
-    int64_t delta;
+    int64_t delta, max_iters;
+    uint64_t kargs;  // address of the kernel's arguments
+    uint64_t div_magic;  // ceil(2^64 / div) for div >= 2
     // state. It has to stay in scalar registers through every loop: the
     // compiler copies all of it wherever paths meet, and what does not fit is
     // moved to vector lanes and back. So the counters live in LDS (Tally),
@@ -343,7 +345,16 @@ struct Sim {
     int cnt, used;
     int64_t sum_ctx;  // KV tokens of the batch, this iteration's included
     int64_t kv_res;   // KV tokens of all residents
-    int evl;  // per lane: iterations to the next event of the batch's members (see streak)
+    // per lane: iterations to the next completion of the batch's members (under
+    // LTR+ also promotion or demotion), and to the next level crossing
+    int evl, evx;
+    // nothing waits and the batch repeats; the latest run of repeated
+    // iterations reached an arrival or its limit
+    bool alone, due;
+    // The next iteration takes every resident, one token each, and all that
+    // arrived, whole chunks of which have new_tok tokens and new_blk blocks
+    bool join;
+    int new_tok, new_blk;
     uint64_t emit_chunks;  // 64-entry chunks holding batch members or evictions
     bool emit_all;         // ranks moved during formation: visit every chunk
     // Repeated batch: the next iteration's formation would select the same
@@ -377,7 +388,7 @@ struct Sim {
     // needed a few times per request are not worth registers all the time.
     typedef const __attribute__((address_space(4))) SimArgs KArgs;
     DEV KArgs *args() const {
-        uint64_t p = sgpr64((uint64_t)__builtin_amdgcn_kernarg_segment_ptr());
+        uint64_t p = kargs;
         __asm__ volatile("" : "+s"(p));  // a new value each time: nothing to keep
         return (KArgs *)p;
     }
@@ -404,7 +415,10 @@ struct Sim {
             int w = 0)
         : A(a) {
         inst = i, trace = st.trace;
-        N = a.n_req, M = a.M, Kb = a.Kb, bs = a.bs, lcap = a.list_cap;
+        kargs = sgpr64((uint64_t)__builtin_amdgcn_kernarg_segment_ptr());
+        N = a.n_req, M = a.M, T = a.T, c = a.c, Kb = a.Kb, bs = a.bs, lcap = a.list_cap;
+        base = a.base, tok = a.tok, div = a.div, div_magic = a.div_magic;
+        max_iters = a.max_iters;
         k = st.k > 0 ? st.k : 1;
         lk = 31 - __clz(k);
         pol = st.policy;
@@ -422,7 +436,7 @@ struct Sim {
         S.k = (uint64_t *)(smem + o), o += (size_t)cap * 8;
         S.tg = (uint2 *)(smem + o), o += (size_t)cap * 8;
         S.bt = (int64_t *)(smem + o), o += (size_t)kLevels * 8;
-        for (int j = lane(); j < kLevels; j += kWave) S.bt[j] = st.bt[j];
+        if (lane() < kLevels) S.bt[lane()] = st.bt[lane()];
         ad = nullptr;
         bnd = 0.0;
         phase_signal = EXT && st.signal == 1;
@@ -452,7 +466,9 @@ struct Sim {
         ev_vol = ev_forced = fpass = 0;
         cnt = used = 0;
         sum_ctx = kv_res = 0;
-        evl = INT32_MAX;
+        evl = evx = INT32_MAX;
+        alone = due = join = false;
+        new_tok = new_blk = 0;
         emit_chunks = 0;
         emit_all = false;
         rep = all_emit = false;
@@ -549,26 +565,18 @@ struct Sim {
             return lcap;
         }
     }
-    // The cost model, read from the kernel arguments (see args).
-    struct Cost {
-        int base, tok, div;
-        uint64_t div_magic;  // ceil(2^64 / div) for div >= 2
-        // floor(s / div). Below 2^32 a multiply by the rounded-up reciprocal is
-        // exact: s * ceil(2^64/div) / 2^64 exceeds s/div by less than 2^-32 <= 1/div.
-        DEV uint64_t quot(uint64_t s) const {
-            if (div == 1) return s;
-            if (s >> 32) return s / (uint64_t)div;
-            const uint32_t x = (uint32_t)s;
-            return ((uint64_t)x * (div_magic >> 32) + __umulhi(x, (uint32_t)div_magic)) >> 32;
-        }
-        DEV int64_t fixed(int tokens) const { return (int64_t)base + (int64_t)tok * tokens; }
-    };
-    DEV Cost cost_model() const {
-        KArgs *a = args();
-        Cost c;
-        c.base = a->base, c.tok = a->tok, c.div = a->div, c.div_magic = a->div_magic;
-        return c;
+    // floor(s / div). Below 2^32 a multiply by the rounded-up reciprocal is
+    // exact: s * ceil(2^64/div) / 2^64 exceeds s/div by less than 2^-32 <= 1/div.
+    DEV uint64_t ctx_quot(uint64_t s) const {
+        if (s >> 32) return s / (uint64_t)div;
+        return ctx_quot32((uint32_t)s);
     }
+    DEV uint32_t ctx_quot32(uint32_t x) const {
+        if (div == 1) return x;
+        return (uint32_t)(((uint64_t)x * (div_magic >> 32) + __umulhi(x, (uint32_t)div_magic)) >> 32);
+    }
+    // the cost of an iteration of `tokens` tokens without its context term
+    DEV int64_t fixed_cost(int tokens) const { return (int64_t)base + (int64_t)tok * tokens; }
     // The signal at which level `lvl` ends, k 2^(lvl+1) (signals stay below
     // 2^24: INT32_MAX for a threshold beyond, and above the last level).
     DEV int next_level(int lvl) const {
@@ -601,19 +609,25 @@ struct Sim {
     // dispatched to the replica so far
     DEV int n_known() const { return CL ? Nk : N; }
 
+    // Without a branch on the lane: the compiler merges the join of such a
+    // branch with the caller's, and then takes scalar state (pf, next and all
+    // that follows from them) for lane-dependent and keeps it in vector
+    // registers.
     DEV void load_pf() {
-        const int r = pf + lane();
-        if (r < n_known()) {
-            if constexpr (CL) {
-                pidx = __hip_atomic_load(&jl()[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                pa = arr()[pidx], pP = Pp()[pidx], pD = Dp()[pidx];
-            } else {
-                pa = arr()[r], pP = Pp()[r], pD = Dp()[r];
+        const int n = n_known(), r = pf + lane();
+        const bool in = r < n;
+        int at = min(r, n - 1);
+        if constexpr (CL) {
+            if (n == 0) {  // nothing dispatched yet
+                pa = INT64_MAX, pP = 1, pD = 1, pidx = 0;
+                return;
             }
-        } else {
-            pa = INT64_MAX, pP = 1, pD = 1;
-            if constexpr (CL) pidx = 0;
+            at = __hip_atomic_load(&jl()[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            pidx = in ? at : 0;
         }
+        const int64_t a = arr()[at];
+        const int p = Pp()[at], d = Dp()[at];
+        pa = in ? a : INT64_MAX, pP = in ? p : 1, pD = in ? d : 1;
     }
 
     DEV R new_record(int idx, int64_t a, int P, int D) const {
@@ -659,6 +673,9 @@ struct Sim {
             const R x = new_record(CL ? pidx : r, pa, pP, pD);
             const R y = off ? shfl_rec(x, min(off + lane(), kWave - 1)) : x;
             arr_pk = min(arr_pk, lane() < n_arr ? y.pk : ~0ull);
+            const int n0 = lane() < n_arr ? min(y.w, c) : 0, b0 = blocks(n0);
+            new_tok += n_arr == 1 ? rl(n0, 0) : wsum(n0);
+            new_blk += n_arr == 1 ? rl(b0, 0) : wsum(b0);
             nW += n_arr;
             next += n_arr;
             add_entries(y, n_arr);
@@ -1003,16 +1020,15 @@ struct Sim {
     // finds the tokens scheduled this iteration already counted).
     DEV void admit_one(int q, uint32_t g, int n, int du, int kvv, int wq, int64_t &ctx_one) {
         const bool res = (g & G_RES) != 0;
-        if (lane() == 0) {
-            uint32_t g2 = g | G_INB;
-            if (!res) g2 = (g2 & ~G_GUARD) | G_RES | ((g >> G_LVL_SHIFT) & 31u);
-            stxkv(q, g2, wq, kvv + n);
-        }
+        const int kv2 = uni(kvv + n);  // (wave-uniform also after the masked store)
+        uint32_t g2 = g | G_INB;
+        if (!res) g2 = (g2 & ~G_GUARD) | G_RES | ((g >> G_LVL_SHIFT) & 31u);
+        if (lane() == 0) stxkv(q, g2, wq, kv2);
         wsync();
         cnt++;
         used += n;
         U += du;
-        ctx_one += kvv + n;
+        ctx_one += kv2;
         if (!res) {
             nW--, nR++;
             vm_set(q, true);
@@ -1102,13 +1118,11 @@ struct Sim {
         // the next chunk's records, loaded while this one is processed; valid
         // while formation walks whole chunks without touching the list
         const int lim = lcap + kStage;
-        KArgs *const ka = args();
-        const int T = ka->T, c = ka->c;
-        const uint32_t max_pass = (uint32_t)lim + (uint32_t)ka->spill_cap + 2u;
+        const uint32_t max_pass = (uint32_t)lim + (uint32_t)spill_n + 2u;
         uint4 nx = make_uint4(0u, 0u, 0u, 0u);
         bool have_nx = false;
         // every pass advances p or refills from the spill, so the walk ends
-        // within L + spill_cap passes; a walk that does not is a broken state
+        // within L + spill_n passes; a walk that does not is a broken state
         for (;;) {
             if (UNLIKELY(!closed && p >= bstar)) {  // bstar <= L: spilled entries come next
                 if (UNLIKELY((uint32_t)++fpass > max_pass)) {
@@ -1230,18 +1244,22 @@ struct Sim {
 
     // ---------------------------------------------------------- execute
 
-    // Returns the lowest rank whose key moved (INT32_MAX if none).
-    DEV int emission(int64_t t_end) {
+    // Returns the lowest rank whose key moved (INT32_MAX if none). `all_in`:
+    // there was no formation, every live entry is a member (see join) and is
+    // admitted here.
+    DEV int emission(int64_t t_end, bool all_in) {
         int lo = INT32_MAX, lohole = INT32_MAX, nd = 0, ufree = 0, kfree = 0, nmv = 0;
         nmoved = 0, n_chunks = 0;
-        evl = INT32_MAX;
+        evl = evx = INT32_MAX;
+        int opened = 0;  // all_in: blocks that residents opened
         bool bad_idx = false;
         uint64_t noemit = 0;  // batch members that emitted no token
         const uint32_t t32 = (uint32_t)t_end;
         const int nch = (L + kWave - 1) >> 6;
         // LTR+ updates every candidate's starvation count: visit every chunk
-        const bool all = emit_all || (EXT && pol == P_LTR);
-        uint64_t todo = all ? (nch >= 64 ? ~0ull : ((1ull << nch) - 1ull)) : emit_chunks;
+        if (all_in || emit_all || (EXT && pol == P_LTR))
+            emit_chunks = nch >= 64 ? ~0ull : ((1ull << nch) - 1ull);
+        uint64_t todo = emit_chunks;
         if (!todo) return INT32_MAX;
         n_chunks = popc(todo);
         // chunks are visited in ascending order, the next one's records loaded
@@ -1267,7 +1285,17 @@ struct Sim {
                 qn = ldq(i1), pkn = S.k[i1], tgn = S.tg[i1];
             }
             const int r = b + lane();
-            const uint32_t g = r < L ? q.x : 0u;
+            uint32_t g = r < L ? q.x : 0u;
+            int kv = skv(q);  // includes this iteration's chunk (added at admission)
+            int now = uni(all_in ? 1 : 0);
+            __asm__("" : "+s"(now));  // (the loop is not to be compiled twice)
+            if (now) {
+                const bool live = r < L && !(g & G_DONE), res = (g & G_RES) != 0;
+                opened += popc(ballot(res && blocks(kv + 1) != blocks(kv)));
+                kv += live ? min(sw(q) - kv, c) : 0;
+                if (!res) g = (g & ~G_GUARD) | ((g >> G_LVL_SHIFT) & 31u);
+                g |= live ? G_INB | G_RES : 0u;
+            }
             // Per lane, as selects: the flag tests below are lane-dependent,
             // and a branch on them would cost scalar exec-mask work in every
             // chunk. Members advance; entries evicted in
@@ -1275,7 +1303,6 @@ struct Sim {
             const bool memb = (g & G_INB) != 0;
             const bool evi = !memb && (g & G_EVI) != 0;
             int w = sw(q), left = sleft(q);
-            int kv = skv(q);  // includes this iteration's chunk (added at admission)
             const int idx = idx_of(pk);
             bad_idx = bad_idx || (memb && idx >= N);
             const bool emit = memb && kv == w && idx < N;
@@ -1326,7 +1353,7 @@ struct Sim {
                 const bool up = sig >= thr;
                 ln += up ? 1 : 0;
                 chg = live && ln != lo_;
-                ev = min(ev, (thr << (up ? 1 : 0)) - sig);
+                if (live) evx = min(evx, (thr << (up ? 1 : 0)) - sig);
                 if (chg) {  // a level crossing (rare): re-key by the table step
                     pk2 = pack(key_of(pk) + S.bt[lo_] - S.bt[ln], idx);
                     gs = (gs & ~G_LVL) | ((uint32_t)ln << G_LVL_SHIFT);
@@ -1412,6 +1439,8 @@ struct Sim {
         if (ballot(bad_idx)) fail(S_ESTATE);
         all_emit = noemit == 0;
         nmoved = nmv;
+        if (all_in) U += opened + new_blk;
+        maxU = max(maxU, U);
         if (nd) {
             const int kf = wsum(kfree);
             U -= wsum(ufree);
@@ -1427,7 +1456,8 @@ struct Sim {
     // A run of repeated iterations (rep): the members are the first nb
     // residents, each takes one token per iteration, and nothing else changes until the
     // first event - a completion, a key that moves otherwise than with all
-    // the others (a level crossing, an LTR+ promotion or demotion), an
+    // the others (an LTR+ promotion or demotion, with requests waiting also a
+    // level crossing), an
     // arrival, a KV budget that the next blocks would exceed, `limit`
     // (CL), a new grid cell (adaptive gamma) or the iteration limit. The
     // outcome of r such iterations has a closed form per member, so they are
@@ -1458,19 +1488,20 @@ struct Sim {
             }
             room = min(room, sat31(rl64(pa, off) - t));
         }
-        const Cost cm_ = cost_model();
-        const int64_t fixed = cm_.fixed(nb);
+        const int64_t fixed = fixed_cost(nb);
         const int64_t top = sum_ctx + (int64_t)kWave * nb;  // the context of iteration 64
         if (UNLIKELY(((uint64_t)fixed >> 24) || (top >> 32))) return 0;
-        const uint64_t qt = cm_.quot((uint64_t)(sum_ctx + (int64_t)(lane() + 1) * nb));
-        if (UNLIKELY((uint32_t)rl((int)(uint32_t)qt, 63) >= (1u << 24))) return 0;
+        const uint32_t qt = ctx_quot32((uint32_t)sum_ctx + (uint32_t)((lane() + 1) * nb));
+        if (UNLIKELY((uint32_t)rl((int)qt, 63) >= (1u << 24))) return 0;
         const int cost = (int)fixed + (int)qt;
         const int tend = scan_add(cost);  // below 64 * 2^25
         int r = kWave;
         const uint64_t late = ballot(tend >= room);  // (a saturated room is never reached)
         if (late) r = ffs0(late) + 1;
-        r = min(r, sat31(args()->max_iters - iters));
-        r = min(r, wmin(evl));
+        r = min(r, sat31(max_iters - iters));
+        // (while nothing waits, the order of the members does not matter: keys
+        // move at the end of the run, and entries are re-inserted later)
+        r = min(r, wmin(alone ? evl : min(evl, evx)));
         if (r <= 0) return 0;
         // KV: every iteration's new blocks fit (the growth only adds up, so the
         // last one's total decides); halved until they do
@@ -1492,6 +1523,7 @@ struct Sim {
             }
         }
         // apply r iterations
+        due = rl(tend, r - 1) >= room;
         const int64_t t_end = t + rl(tend, r - 1);
         const uint32_t t32 = (uint32_t)t_end, gap = (uint32_t)rl(cost, r - 1);  // costs never shrink
         int lohole = INT32_MAX, nd = 0, grow = 0, ufree = 0, kfree = 0;
@@ -1499,7 +1531,7 @@ struct Sim {
         const int nch = (L + kWave - 1) >> 6;
         const uint64_t chunks =
             EXT && pol == P_LTR ? (nch >= 64 ? ~0ull : ((1ull << nch) - 1ull)) : emit_chunks;
-        evl = INT32_MAX;
+        evl = evx = INT32_MAX;
         for (uint64_t todo = chunks; todo; todo &= todo - 1) {
             const int b = ffs0(todo) * kWave;
             const int i = b + lane(), i0 = min(i, L - 1);
@@ -1549,17 +1581,19 @@ struct Sim {
                         sig -= phase_signal ? Pp()[ix] : Hp()[ix];
                     }
                 }
-                const int thr = next_level(ol);
+                int thr = next_level(ol);
                 const bool chg = memb && !fin && sig >= thr;
-                ev = min(ev, (thr << (chg ? 1 : 0)) - sig);
                 cm = ballot(chg);
                 if (cm) {
                     const uint64_t pk = S.k[i0];
                     if (chg) {
-                        S.k[i] = pack(key_of(pk) + S.bt[ol] - S.bt[ol + 1], idx_of(pk));
-                        gs = (gs & ~G_LVL) | ((uint32_t)(ol + 1) << G_LVL_SHIFT) | G_DIRTY;
+                        const int nl = level_of(sig, k, lk);
+                        thr = next_level(nl);
+                        S.k[i] = pack(key_of(pk) + S.bt[ol] - S.bt[nl], idx_of(pk));
+                        gs = (gs & ~G_LVL) | ((uint32_t)nl << G_LVL_SHIFT) | G_DIRTY;
                     }
                 }
+                if (memb && !fin) evx = min(evx, thr - sig);
             } else if (pol == P_SRPT || pol == P_TRAIL || pol == P_LAS) {
                 // every member's key moves by r; holes among them move along, so
                 // that the residents and holes stay in order
@@ -2016,7 +2050,7 @@ struct Sim {
     // The batch just formed respects the sequence cap, the token budget and
     // the KV budget, and every member computes at least one token.
     DEV void check_batch() {
-        if (cnt < 1 || cnt > M || used < cnt || used > args()->T || U < 0 || U > Kb) fail(S_ESTATE);
+        if (cnt < 1 || cnt > M || used < cnt || used > T || U < 0 || U > Kb) fail(S_ESTATE);
     }
 
     // The state between iterations: the list's residents, waiting entries
@@ -2125,29 +2159,63 @@ struct Sim {
         return false;
     }
 
+    // Nothing waited and every resident needs one token; then requests
+    // arrived. If they all fit beside the residents, the next iteration
+    // takes everything, in whatever order: emission admits it in its pass and
+    // no formation is needed.
+    DEV void plan_join() {
+        join = nW > 0 && spill_n == 0 && nR + nW <= M && new_tok <= T - nR &&
+               nR + new_blk <= Kb - U;
+    }
+
     // One iteration, or a run of repeated ones; then the list's maintenance
     // and the arrivals. `limit`: see streak.
     DEV void step(int64_t limit) {
-        sum_ctx = (int64_t)sgpr64((uint64_t)sum_ctx);
-        const int c0 = completed, next0 = next, sp0 = n_spilled;
-        int lo_mod = INT32_MAX;
+        const int c0 = completed;
+        int lo_mod;
         // Does the next iteration repeat this one's batch? `again`: every
         // member emitted a token, so each needs exactly one next; `whole`:
         // the members are all the residents; `stays`: formation evicted
         // nothing, refilled nothing and stopped short of the token budget.
         bool again = true, whole = last == INT32_MAX || nb == nR, stays = true;
-        if (!(rep && streak(limit, lo_mod) > 0)) {
+        bool run = false;
+        int lo_pend = INT32_MAX, nm_pend = 0;  // entries to re-insert: lowest rank, how many
+        while (rep) {
+            const int c1 = completed;
+            int lo;
+            if (streak(limit, lo) == 0) break;
+            run = true;
+            lo_pend = min(lo_pend, lo);
+            nm_pend += nmoved;
+            last_done = completed - c1;
+            // nothing waits or arrived: straight on, the order can wait
+            if (!alone || due || nR == 0 || n_holes >= kHoleLimit) break;
+            nb = nR;
+        }
+        if (run) {
+            lo_mod = lo_pend, nmoved = nm_pend;
+        } else {
             if constexpr (EXT) {
                 if (ad) {
                     ada_update();
                     if (status) return;
                 }
             }
-            formation();
-            if (status) return;
-            if (cnt == 0) {
-                fail(S_ESTATE);
-                return;
+            if (join) {
+                cnt = nR + nW, used = nR + new_tok;
+                nR += nW, nW = 0;
+                kv_res += used;
+                sum_ctx = kv_res;
+                close_pk = ~0ull;
+                ev_vol = ev_forced = fpass = 0;
+                emit_all = vm_ok = false;
+            } else {
+                formation();
+                if (status) return;
+                if (cnt == 0) {
+                    fail(S_ESTATE);
+                    return;
+                }
             }
             if constexpr (kCheck) {
                 check_batch();
@@ -2155,23 +2223,26 @@ struct Sim {
             }
             whole = cnt == nR;
             nb = cnt;
-            stays = ev_vol + ev_forced == 0 && !emit_all && used < args()->T;
-            maxU = max(maxU, U);
-            const Cost cost = cost_model();
-            const int64_t dt = cost.fixed(used) + (int64_t)cost.quot((uint64_t)sum_ctx);
+            stays = ev_vol + ev_forced == 0 && !emit_all && used < T;
+            const int64_t dt = fixed_cost(used) + (int64_t)ctx_quot((uint64_t)sum_ctx);
             const int64_t t_end = t + dt;
-            lo_mod = emission(t_end);
+            const int c1 = completed;
+            lo_mod = emission(t_end, join);
+            last_done = completed - c1;
+            join = false;
             again = all_emit;
             t = t_end;
             iters++;
             tally(cnt, used, 4 + 5 * fpass + 3 * n_chunks);
-            if (less64(args()->max_iters, iters)) {
+            if (less64(max_iters, iters)) {
                 fail(S_ELIVELOCK);
                 return;
             }
         }
-        if constexpr (CL) last_done = completed - c0;
+        const int next0 = next, sp0 = n_spilled;
+        const bool none = nW == 0 && spill_n == 0;  // nothing waited before the arrivals
         arr_pk = ~0ull;
+        new_tok = new_blk = 0;
         const bool edited = maintenance(lo_mod);
         // A whole batch repeats (as far as the KV budget allows: see streak)
         // if nothing waits. With requests waiting, or residents left out of
@@ -2189,7 +2260,7 @@ struct Sim {
         // do as long as no resident is left out and no waiting request ranks
         // before them (it takes no victims by priority). LAS's grow, past
         // the waiting ones: excluded.
-        const bool alone = whole && nW == 0 && spill_n == 0;
+        alone = whole && nW == 0 && spill_n == 0;
         bool ok = stays && completed == c0 && pol != P_LAS && n_spilled == sp0 &&
                   (whole || nb == M);
         if (lo_mod != INT32_MAX && pol != P_SRPT && pol != P_TRAIL) {
@@ -2208,6 +2279,8 @@ struct Sim {
                 rep = arrivals_keep(next0, edited || emit_all || next != next0);
             }
         }
+        alone = alone && rep;
+        if (!rep && again && whole && none) plan_join();
         if constexpr (kCheck) {
             if (status == 0) check_state();
         }
@@ -2254,8 +2327,14 @@ struct Sim {
         if (status) return;
         const int next0 = next, sp0 = n_spilled;
         arr_pk = ~0ull;
+        if (!join) new_tok = new_blk = 0;
         take_arrivals();  // the router may have dispatched since the last call
-        if (rep && next != next0) rep = n_spilled == sp0 && arrivals_keep(next0, true);
+        if (next != next0) {
+            const bool free_ = alone || join;  // every resident needs one token
+            rep = rep && n_spilled == sp0 && arrivals_keep(next0, true);
+            alone = false;
+            if (!rep && free_) plan_join();
+        }
         for (;;) {
             if (status) return;
             if (UNLIKELY(nW + nR == 0)) {
