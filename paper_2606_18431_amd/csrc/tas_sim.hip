@@ -115,6 +115,25 @@ DEV uint64_t sgpr64(uint64_t x) {
     const uint32_t lo = (uint32_t)uni((int)(uint32_t)x), hi = (uint32_t)uni((int)(uint32_t)(x >> 32));
     return ((uint64_t)hi << 32) | lo;
 }
+// A wave-uniform value kept in a vector register: state and constants that a
+// step uses once or twice. Scalar registers are what the simulator runs out
+// of, and a spilled scalar costs a lane write and a lane read where the
+// compiler chooses; there are vector registers to spare at the occupancy the
+// LDS allows. `v` serves lane arithmetic as it is, the conversion gives the
+// scalar.
+template <typename T_>
+struct Held {
+    T_ v;
+    DEV Held &operator=(T_ x) {
+        v = x;
+        __asm__("" : "+v"(v));
+        return *this;
+    }
+    DEV operator T_() const {
+        if constexpr (sizeof(T_) == 8) return (T_)sgpr64((uint64_t)v);
+        else return (T_)uni((int)v);
+    }
+};
 // x with lane LANE set to the wave-uniform v
 template <int LANE>
 DEV int set_lane(int x, int v) {
@@ -318,11 +337,12 @@ struct Sim {
     const SimArgs &A;
     Lds S;
     // instance constants (memguard and delta are zero unless pol is BOOST)
-    int inst, trace, N, M, T, c, Kb, bs, base, tok, div, pol, k, lk, memguard, lcap;
+    Held<int> inst, trace, N, c, base, tok, div, k, lk;
+    int M, T, Kb, bs, pol, memguard, lcap;
     int ltr_s, ltr_q;  // LTR+: starvation threshold and quantum (iterations)
-    int64_t delta, max_iters;
-    uint64_t kargs;  // address of the kernel's arguments
-    uint64_t div_magic;  // ceil(2^64 / div) for div >= 2
+    Held<int64_t> delta, max_iters;
+    Held<uint64_t> kargs;  // address of the kernel's arguments
+    Held<uint64_t> div_magic;  // ceil(2^64 / div) for div >= 2
     // state. It has to stay in scalar registers through every loop: the
     // compiler copies all of it wherever paths meet, and what does not fit is
     // moved to vector lanes and back. So the counters live in LDS (Tally),
@@ -333,8 +353,8 @@ struct Sim {
     uint64_t spill_min;
     int64_t pa;
     int pP, pD;
-    int64_t iters;
-    int maxU;
+    Held<int64_t> iters;
+    Held<int> maxU;
     int ev_vol, ev_forced, fpass;  // evictions and passes of the latest formation
     // CL: the replica (wave) index, the global indices dispatched to it in
     // order (HBM, written and read by this wave only, through L2), how many,
@@ -414,13 +434,20 @@ struct Sim {
     DEV Sim(const SimArgs &a, const DevSetting &st, int i, unsigned char *smem, uint64_t *tally,
             int w = 0)
         : A(a) {
-        inst = i, trace = st.trace;
+        inst = i;
+        trace = st.trace;
         kargs = sgpr64((uint64_t)__builtin_amdgcn_kernarg_segment_ptr());
-        N = a.n_req, M = a.M, T = a.T, c = a.c, Kb = a.Kb, bs = a.bs, lcap = a.list_cap;
-        base = a.base, tok = a.tok, div = a.div, div_magic = a.div_magic;
+        N = a.n_req;
+        c = a.c;
+        M = a.M, T = a.T, Kb = a.Kb, bs = a.bs, lcap = a.list_cap;
+        base = a.base;
+        tok = a.tok;
+        div = a.div;
+        div_magic = a.div_magic;
         max_iters = a.max_iters;
-        k = st.k > 0 ? st.k : 1;
-        lk = 31 - __clz(k);
+        const int k0 = st.k > 0 ? st.k : 1;
+        k = k0;
+        lk = 31 - __clz(k0);
         pol = st.policy;
         ltr_s = st.ltr_s, ltr_q = st.ltr_q;
         memguard = st.memguard;
@@ -462,7 +489,8 @@ struct Sim {
         U = L = nW = nR = n_holes = spill_n = next = pf = completed = status = 0;
         lo_hole = INT32_MAX;
         spill_min = ~0ull;
-        iters = 0, maxU = 0;
+        iters = 0;
+        maxU = 0;
         ev_vol = ev_forced = fpass = 0;
         cnt = used = 0;
         sum_ctx = kv_res = 0;
@@ -568,7 +596,7 @@ struct Sim {
     // floor(s / div). Below 2^32 a multiply by the rounded-up reciprocal is
     // exact: s * ceil(2^64/div) / 2^64 exceeds s/div by less than 2^-32 <= 1/div.
     DEV uint64_t ctx_quot(uint64_t s) const {
-        if (s >> 32) return s / (uint64_t)div;
+        if (s >> 32) return s / (uint64_t)(int)div;
         return ctx_quot32((uint32_t)s);
     }
     DEV uint32_t ctx_quot32(uint32_t x) const {
@@ -580,7 +608,7 @@ struct Sim {
     // The signal at which level `lvl` ends, k 2^(lvl+1) (signals stay below
     // 2^24: INT32_MAX for a threshold beyond, and above the last level).
     DEV int next_level(int lvl) const {
-        return k <= (0xffffff >> (lvl + 1)) ? k << (lvl + 1) : INT32_MAX;
+        return k.v <= (0xffffff >> (lvl + 1)) ? k.v << (lvl + 1) : INT32_MAX;
     }
     DEV int blocks(int x) const {
         if constexpr (BSH >= 0) {
@@ -647,9 +675,9 @@ struct Sim {
             int sig = P;  // the signal before the first token
             if constexpr (EXT) {
                 // cached tokens are not work (lanes past the trace hold no request)
-                if (cache_signal && idx < N) sig = P - Hp()[idx];
+                if (cache_signal && idx < N.v) sig = P - Hp()[idx];
             }
-            lvl = (uint32_t)level_of(sig, k, lk);
+            lvl = (uint32_t)level_of(sig, k.v, lk.v);
             key = a - S.bt[lvl];
         }
         x.gs = lvl << G_LVL_SHIFT;
@@ -673,7 +701,7 @@ struct Sim {
             const R x = new_record(CL ? pidx : r, pa, pP, pD);
             const R y = off ? shfl_rec(x, min(off + lane(), kWave - 1)) : x;
             arr_pk = min(arr_pk, lane() < n_arr ? y.pk : ~0ull);
-            const int n0 = lane() < n_arr ? min(y.w, c) : 0, b0 = blocks(n0);
+            const int n0 = lane() < n_arr ? min(y.w, c.v) : 0, b0 = blocks(n0);
             new_tok += n_arr == 1 ? rl(n0, 0) : wsum(n0);
             new_blk += n_arr == 1 ? rl(b0, 0) : wsum(b0);
             nW += n_arr;
@@ -939,7 +967,7 @@ struct Sim {
                 int64_t Dv = 0, lv = 0;
                 if (rs) {
                     const int idx = idx_of(S.k[r]);
-                    Dv = idx < N ? Dp()[idx] : 0;
+                    Dv = idx < N.v ? Dp()[idx] : 0;
                     lv = CP ? (int)(g >> kLeftShift) + 1 : (int)S.q[r].w;
                 }
                 ev = rs && !(2 * Dv >= 5 * lv);
@@ -1152,7 +1180,7 @@ struct Sim {
             const int kvv = skv(qr);
             const bool res = (g & G_RES) != 0;
             const bool cand = valid && !(g & (G_EVI | G_DONE)) && (res || !closed);
-            const int m = cand ? min(w - kvv, c) : 0;
+            const int m = cand ? min(w - kvv, c.v) : 0;
             const int d = cand ? blocks(kvv + m) - blocks(kvv) : 0;
             const uint64_t cm = ballot(cand), resm = ballot(res);
             int mt = 0, dt = 0;  // tokens and blocks of the lanes admitted
@@ -1251,6 +1279,8 @@ struct Sim {
         int lo = INT32_MAX, lohole = INT32_MAX, nd = 0, ufree = 0, kfree = 0, nmv = 0;
         nmoved = 0, n_chunks = 0;
         evl = evx = INT32_MAX;
+        int64_t it_end = 0;
+        if constexpr (EXT) it_end = (int64_t)sgpr64((uint64_t)(iters + 1));
         int opened = 0;  // all_in: blocks that residents opened
         bool bad_idx = false;
         uint64_t noemit = 0;  // batch members that emitted no token
@@ -1292,7 +1322,7 @@ struct Sim {
             if (now) {
                 const bool live = r < L && !(g & G_DONE), res = (g & G_RES) != 0;
                 opened += popc(ballot(res && blocks(kv + 1) != blocks(kv)));
-                kv += live ? min(sw(q) - kv, c) : 0;
+                kv += live ? min(sw(q) - kv, c.v) : 0;
                 if (!res) g = (g & ~G_GUARD) | ((g >> G_LVL_SHIFT) & 31u);
                 g |= live ? G_INB | G_RES : 0u;
             }
@@ -1304,8 +1334,8 @@ struct Sim {
             const bool evi = !memb && (g & G_EVI) != 0;
             int w = sw(q), left = sleft(q);
             const int idx = idx_of(pk);
-            bad_idx = bad_idx || (memb && idx >= N);
-            const bool emit = memb && kv == w && idx < N;
+            bad_idx = bad_idx || (memb && idx >= N.v);
+            const bool emit = memb && kv == w && idx < N.v;
             const bool first = emit && !(g & G_FIRST);
             // times are kept modulo 2^32: a gap of 2^32 us or more overflows
             // the request's TTLT too
@@ -1342,10 +1372,10 @@ struct Sim {
                 int ln = lo_;
                 if constexpr (EXT) {
                     // every lane reads: keep non-member lanes in bounds
-                    const int ix = min(idx, N - 1);
+                    const int ix = min(idx, N.v - 1);
                     if (phase_signal) sig = w - Pp()[ix];  // dec >= 1 after this token
                     if (cache_signal) sig = w - Hp()[ix];  // P - h + dec
-                    if (phase_signal) ln = level_of(sig, k, lk);  // may fall at the first token
+                    if (phase_signal) ln = level_of(sig, k.v, lk.v);  // may fall at the first token
                 }
                 // the signal grows by one a token: the level follows when it
                 // reaches the next threshold
@@ -1401,7 +1431,7 @@ struct Sim {
                     if ((int)cnt >= ltr_s) {
                         gx = (g & G_FLAGS & ~G_EVI) | G_PROMO | G_DIRTY |
                              ((uint32_t)ltr_q << kLtrShift);
-                        pk2 = pack(iters + 1 - kPromotedOff, idx);
+                        pk2 = pack(it_end - kPromotedOff, idx);
                         S.k[r] = pk2;
                         chg = true;
                     } else {
@@ -1440,7 +1470,7 @@ struct Sim {
         all_emit = noemit == 0;
         nmoved = nmv;
         if (all_in) U += opened + new_blk;
-        maxU = max(maxU, U);
+        maxU = max(maxU.v, U);
         if (nd) {
             const int kf = wsum(kfree);
             U -= wsum(ufree);
@@ -1522,7 +1552,9 @@ struct Sim {
                 if (r == 0) return 0;
             }
         }
-        // apply r iterations
+        // apply r iterations (counted before the loop: a sum the compiler also finds
+        // in a lane's branch would make the count lane-dependent)
+        const int64_t it_end = (int64_t)sgpr64((uint64_t)(iters + r));
         due = rl(tend, r - 1) >= room;
         const int64_t t_end = t + rl(tend, r - 1);
         const uint32_t t32 = (uint32_t)t_end, gap = (uint32_t)rl(cost, r - 1);  // costs never shrink
@@ -1577,7 +1609,7 @@ struct Sim {
                 int sig = w;
                 if constexpr (EXT) {
                     if (phase_signal || cache_signal) {
-                        const int ix = min(idx_of(S.k[i0]), N - 1);
+                        const int ix = min(idx_of(S.k[i0]), N.v - 1);
                         sig -= phase_signal ? Pp()[ix] : Hp()[ix];
                     }
                 }
@@ -1587,7 +1619,7 @@ struct Sim {
                 if (cm) {
                     const uint64_t pk = S.k[i0];
                     if (chg) {
-                        const int nl = level_of(sig, k, lk);
+                        const int nl = level_of(sig, k.v, lk.v);
                         thr = next_level(nl);
                         S.k[i] = pack(key_of(pk) + S.bt[ol] - S.bt[nl], idx_of(pk));
                         gs = (gs & ~G_LVL) | ((uint32_t)nl << G_LVL_SHIFT) | G_DIRTY;
@@ -1607,6 +1639,7 @@ struct Sim {
                 if (pol == P_SARATHI) {  // all to the same, latest key: they stay in order
                     const int idx = idx_of(S.k[i0]);
                     if (memb && !fin) S.k[i] = pack(t_end - kDecodeQueueOff, idx);
+                    wsync();  // (joins the lanes before the branches on the policy do)
                 } else if (pol == P_LTR) {
                     bool chg = false;
                     const uint64_t pk = S.k[i0];
@@ -1629,7 +1662,7 @@ struct Sim {
                         if ((int)c2 >= ltr_s) {  // promoted at the end of the r-th iteration
                             gx = (g & G_FLAGS) | G_PROMO | G_DIRTY |
                                  ((uint32_t)ltr_q << kLtrShift);
-                            S.k[i] = pack(iters + r - kPromotedOff, idx_of(pk));
+                            S.k[i] = pack(it_end - kPromotedOff, idx_of(pk));
                             chg = true;
                         } else {
                             evl = min(evl, ltr_s - (int)c2);
@@ -1651,12 +1684,12 @@ struct Sim {
         }
         wsync();
         if (pol == P_TRAIL) vm_ok = false;  // eligibility depends on progress
-        iters += r;
+        iters = it_end;
         ev_vol = ev_forced = 0;
         tally(r * nb, r * nb, 4 + 3 * popc(chunks));
         sum_ctx += r * nb, kv_res += r * nb;
         U += grow;
-        maxU = max(maxU, U);
+        maxU = max(maxU.v, U);
         if (nd) {
             const int kf = wsum(kfree);
             U -= wsum(ufree);
@@ -2090,7 +2123,7 @@ struct Sim {
             e = e || (live && (g & G_DIRTY) != 0);
             e = e || (live && pk + 1 <= exc);  // not above a live key before it
             e = e || (done && r < lo_hole);
-            e = e || (live && (kv < 0 || kv > w || left < 1 || idx_of(pk) >= N));
+            e = e || (live && (kv < 0 || kv > w || left < 1 || idx_of(pk) >= N.v));
             e = e || (wt && kv != 0);
             bad = bad || ballot(e) != 0;
             const uint64_t cm = rlu(inc, 63);
@@ -2112,7 +2145,7 @@ struct Sim {
                     const Rec x = spill()[i];
                     if (x.pk < mn) mn = x.pk;
                     e = e || (x.gs & (G_RES | G_DONE | G_INB | G_EVI | G_MARK | G_DIRTY)) != 0 ||
-                        x.kv != 0 || x.left < 1 || idx_of(x.pk) >= N;
+                        x.kv != 0 || x.left < 1 || idx_of(x.pk) >= N.v;
                 }
             }
             bad = ballot(e) != 0 || wminu(mn) != spill_min;
@@ -2232,7 +2265,7 @@ struct Sim {
             join = false;
             again = all_emit;
             t = t_end;
-            iters++;
+            iters = iters.v + 1;
             tally(cnt, used, 4 + 5 * fpass + 3 * n_chunks);
             if (less64(max_iters, iters)) {
                 fail(S_ELIVELOCK);
@@ -2484,7 +2517,8 @@ static_assert(sizeof(JsqLds) == kJsqLdsBytes, "router block size");
 template <int BSH>
 DEV void run_cluster(const SimArgs &a, const DevSetting &st, int inst, unsigned char *smem) {
     JsqLds *J = (JsqLds *)smem;
-    const int R = a.replicas, w = (int)(threadIdx.x >> 6), N = a.n_req;
+    const int R = a.replicas, N = a.n_req;
+    const int w = uni((int)(threadIdx.x >> 6));  // (scalar: the state follows from it)
     Sim<BSH, true, true> s(a, st, inst, smem + kJsqLdsBytes + (size_t)w * (size_t)a.wave_lds,
                            (uint64_t *)J->cn[w], w);
     const int64_t *arr = a.arrival + (size_t)st.trace * (size_t)N;
@@ -2529,16 +2563,15 @@ DEV void run_cluster(const SimArgs &a, const DevSetting &st, int inst, unsigned 
 
 // EXT: the extended build (adaptive gamma, the phase-aware and cache-aware signals,
 // DistBoost, Sarathi), launched when some instance uses one of them (its extra state
-// and code cost the other policies registers). CP: compact list slots.
-template <bool EXT, bool CP>
+// and code cost the other policies registers). CP: compact list slots. BSH: see Sim.
+template <bool EXT, bool CP, int BSH>
 __global__ __launch_bounds__(64) void sim_kernel(SimArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     if ((int)blockIdx.x >= a.n_inst) return;
     const int inst = a.order ? a.order[blockIdx.x] : (int)blockIdx.x;
     if (a.retry && a.status[inst] != S_ECAPACITY) return;
     const DevSetting &st = a.inst[inst];
-    if (a.bs == 16) run_instance<4, EXT, CP>(a, st, inst, smem);
-    else run_instance<-1, EXT, CP>(a, st, inst, smem);
+    run_instance<BSH, EXT, CP>(a, st, inst, smem);
 }
 
 // MAXW: the largest number of waves (replicas) the build serves; 8 leaves
@@ -2586,10 +2619,12 @@ int tas_launch_cluster(const tas::SimArgs &a, int64_t lds_bytes, void *stream) {
 int tas_launch_sim(const tas::SimArgs &a, int64_t lds_bytes, void *stream) {
     if (a.n_inst <= 0) return 0;
     hipStream_t s = (hipStream_t)stream;
-    void (*const fns[2][2])(tas::SimArgs) = {
-        {tas::sim_kernel<false, false>, tas::sim_kernel<false, true>},
-        {tas::sim_kernel<true, false>, tas::sim_kernel<true, true>}};
-    void (*fn)(tas::SimArgs) = fns[a.ext ? 1 : 0][a.cp ? 1 : 0];
+    void (*const fns[2][2][2])(tas::SimArgs) = {
+        {{tas::sim_kernel<false, false, -1>, tas::sim_kernel<false, false, 4>},
+         {tas::sim_kernel<false, true, -1>, tas::sim_kernel<false, true, 4>}},
+        {{tas::sim_kernel<true, false, -1>, tas::sim_kernel<true, false, 4>},
+         {tas::sim_kernel<true, true, -1>, tas::sim_kernel<true, true, 4>}}};
+    void (*fn)(tas::SimArgs) = fns[a.ext ? 1 : 0][a.cp ? 1 : 0][a.bs == 16 ? 1 : 0];
     if (lds_bytes > 65536) {
         if (hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)lds_bytes) != hipSuccess)
