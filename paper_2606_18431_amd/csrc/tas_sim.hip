@@ -1199,7 +1199,30 @@ struct Sim {
             }
             uint64_t okm = cm, bad = 0;
             int n = m, du = d;
-            if (!all) {
+            bool scan = !all;
+            if (scan) {
+                // Up to the first candidate that computes more than a token,
+                // counting lanes gives the prefix sums (two chains of six
+                // dependent lane moves). Where the KV budget binds, the
+                // candidate that does not fit is nearly always among those,
+                // the first waiting one at the latest: 1 % off the chat,
+                // large and comparator sweeps and the clusters, 2 % off the
+                // ragged engine, 0.3 % off the reasoning sweep.
+                const uint64_t big = ballot(m > 1), dm = ballot(d > 0);
+                const uint64_t upto = big ? big ^ (big - 1) : ~0ull;
+                const uint64_t over = ballot(mbcnt(dm) + d > Kb - U) & upto;
+                if (over) {
+                    const int ql = ffs0(over);
+                    const uint64_t before = cm & ((1ull << ql) - 1ull);
+                    const int k = popc(before);
+                    if (cnt + k < M && rl(m, ql) <= T - used - k) {
+                        bad = over, okm = before;
+                        mt = k, dt = popc(dm & before);
+                        scan = false;
+                    }
+                }
+            }
+            if (scan) {
                 // the candidates admitted from this chunk are a prefix of
                 // its candidates, and only the last of them can be clipped
                 // by the token budget
