@@ -134,11 +134,14 @@ struct Held {
         else return (T_)uni((int)v);
     }
 };
-// x with lane LANE set to the wave-uniform v
+// x with lane LANE set to the wave-uniform v. The intrinsic, not inline
+// assembly: v is often reloaded by a lane read just before, a vector
+// instruction may read that scalar only two wait states later, and the
+// compiler inserts them for instructions it knows, not inside assembly text.
+__device__ int llvm_writelane(int v, int l, int x) __asm("llvm.amdgcn.writelane.i32");
 template <int LANE>
 DEV int set_lane(int x, int v) {
-    __asm__("v_writelane_b32 %0, %1, %2" : "+v"(x) : "s"(uni(v)), "n"(LANE));
-    return x;
+    return llvm_writelane(uni(v), LANE, x);
 }
 // x < y for wave-uniform values whose difference fits 63 bits, in scalar
 // instructions.
