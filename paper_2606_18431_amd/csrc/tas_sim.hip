@@ -1509,6 +1509,17 @@ struct Sim {
         return lo;
     }
 
+    // How many members of a repeated batch complete in its r-th iteration.
+    DEV int completing(int r) const {
+        int n = 0;
+        for (uint64_t todo = emit_chunks; todo; todo &= todo - 1) {
+            const int i = ffs0(todo) * kWave + lane();
+            const uint4 q = ldq(min(i, L - 1));
+            n += popc(ballot(i < L && i <= last && (q.x & G_RES) && sleft(q) == r));
+        }
+        return n;
+    }
+
     // A run of repeated iterations (rep): the members are the first nb
     // residents, each takes one token per iteration, and nothing else changes until the
     // first event - a completion, a key that moves otherwise than with all
@@ -1521,8 +1532,10 @@ struct Sim {
     // the context sum, which grows by the members each time: lane j computes
     // the j-th cost and a prefix sum their end times, so the run is at most
     // 64 long. The events of the r-th iteration itself are applied too.
-    // Returns r (0: the next iteration needs a formation; nothing was done)
-    // and sets `lo` to the lowest rank that must be re-inserted.
+    // Returns r (0: the next iteration needs a formation, or the list an
+    // insertion; nothing was done) and sets `lo` to the lowest rank that must
+    // be re-inserted. `unsorted`: an earlier run moved keys, and the entries
+    // were not re-inserted since.
     //
     // What bounds an instance is its own chain of iterations (about 10,000
     // cycles each for one formation and emission, on an idle or a full chip
@@ -1530,7 +1543,7 @@ struct Sim {
     // the iterations of the sweeps below the KV limit repeat the batch before
     // them, 5 to 25 in a row. Eight instances of 1,000 requests went from
     // 147 ms to 11.4 ms, 16,384 instances of 8,000 from 1,181 to 658 ms.
-    DEV int streak(int64_t limit, int &lo) {
+    DEV int streak(int64_t limit, bool unsorted, int &lo) {
         lo = INT32_MAX;
         nmoved = 0;
         // time: the r-th iteration starts before the next arrival and `limit`
@@ -1555,9 +1568,19 @@ struct Sim {
         const uint64_t late = ballot(tend >= room);  // (a saturated room is never reached)
         if (late) r = ffs0(late) + 1;
         r = min(r, sat31(max_iters - iters));
-        // (while nothing waits, the order of the members does not matter: keys
-        // move at the end of the run, and entries are re-inserted later)
+        // (while nothing waits, the order of the members decides nothing but
+        // the order in which latencies enter gamma's window: keys move at the
+        // end of the run, and entries are re-inserted later)
         r = min(r, wmin(alone ? evl : min(evl, evx)));
+        if constexpr (EXT) {
+            // Latencies of one iteration enter the window in the order of the
+            // keys it started with. Where a key moved before it, two requests
+            // that complete in it need the list sorted first: the run ends an
+            // iteration short of them. The adaptive sweep of 4,000 requests
+            // takes 59.5 ms so, 66.1 ms with every run ended at a crossing
+            // (58.2 ms in list order, which is wrong).
+            if (ad && alone && (unsorted || wmin(evx) < r) && completing(r) > 1) r--;
+        }
         if (r <= 0) return 0;
         // KV: every iteration's new blocks fit (the growth only adds up, so the
         // last one's total decides); halved until they do
@@ -2242,7 +2265,7 @@ struct Sim {
         while (rep) {
             const int c1 = completed;
             int lo;
-            if (streak(limit, lo) == 0) break;
+            if (streak(limit, lo_pend != INT32_MAX, lo) == 0) break;
             run = true;
             lo_pend = min(lo_pend, lo);
             nm_pend += nmoved;

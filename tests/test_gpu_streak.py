@@ -114,3 +114,56 @@ def test_crossing_beside_completion(torch, D):  # noqa: F811
     w = edge_workload([0, 0, 10, 20], [2, 2, 9, 3], [D, D + 1, D, 12], e, POLICIES)
     o = oracle.run(w)
     assert_parity(w, gpu_run(w), o)
+
+
+def assert_gamma(g, o):
+    assert np.array_equal(g["gamma"].view(np.int64), o["gamma"].view(np.int64)), (g["gamma"], o["gamma"])
+    assert np.array_equal(g["switches"], o["switches"])
+
+
+@pytest.mark.parametrize("ahead", [0, 1, 2, 20, 63, 64, 65, 130])
+def test_two_completions_after_a_crossing(torch, ahead):  # noqa: F811
+    """Two requests complete in one iteration; the older one crossed a level
+    `ahead` iterations before, which moved it behind the other in the batch.
+    Their latencies enter gamma's window in batch order, and a window that is
+    full later drops the one that entered first: with 21 latencies the
+    largest or the second largest, so that gamma differs by the order."""
+    e = W.Engine(iter_ctx_div=1_000_000, iter_tok_us=0)  # 5 ms an iteration
+    DA, later = 200, 20
+    arr, P, D = [0, later * 5000], [512 - (DA - ahead), 100], [DA, DA - later]
+    for i in range(21):  # then one at a time; the last one decodes on as the window has dropped one
+        arr.append(DA * 5000 + 1000 + 100_000 * i)
+        P.append(16)
+        D.append(90 if i == 20 else 2 + i % 3)
+    ada = dict(W.ADA, window=21, min_samples=20, beta=0.3)
+    w = edge_workload(arr, P, D, e,
+                      [W.setting(0, W.BOOST, gamma=1e-3, ada=dict(ada, window=n), **W.UNIBOOST)
+                       for n in (20, 21, 22)])
+    o = oracle.run(w)
+    done = w.arrival_us[0] + o["ttlt"]
+    assert np.all(done[:, 0] == done[:, 1])
+    g = gpu_run(w)
+    assert_parity(w, g, o)
+    assert_gamma(g, o)
+
+
+@pytest.mark.parametrize("seed,burst,longest", [(24, 25, 200), (12, 10, 600), (6, 50, 100)])
+def test_many_completions_at_once(torch, seed, burst, longest):  # noqa: F811
+    """Bursts of requests that arrive apart and complete together, on every
+    80th iteration, after level crossings in quiet stretches: several
+    latencies enter small windows at once, all the time."""
+    rng = np.random.default_rng(seed)
+    n = 500
+    m = np.sort(np.concatenate([400 * b + rng.integers(0, 60, burst) for b in range(n // burst)]))
+    D = 80 * ((m + rng.integers(30, 300, n)) // 80 + 1) - m
+    e = W.Engine(iter_ctx_div=1_000_000, iter_tok_us=0, max_seqs=300, kv_blocks=100_000)
+    sets = [W.setting(0, W.BOOST, gamma=g0, ada=dict(W.ADA, window=k, min_samples=k // 2 + 1, beta=b),
+                      **kw)
+            for g0 in (1e-4, 1e-2) for k, b in ((21, 0.05), (33, 0.3), (100, 1.0))
+            for kw in (W.UNIBOOST, W.VANILLA, dict(k=7, signal=1))]
+    w = edge_workload(m * 5000, rng.integers(1, longest, n), D, e, sets)
+    o = oracle.run(w)
+    assert np.all(o["status"] == 0) and np.all(o["switches"] > 0)
+    g = gpu_run(w)
+    assert_parity(w, g, o)
+    assert_gamma(g, o)
