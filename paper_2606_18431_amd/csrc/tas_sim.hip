@@ -2413,7 +2413,9 @@ struct Sim {
         take_arrivals();  // the router may have dispatched since the last call
         if (next != next0) {
             const bool free_ = alone || join;  // every resident needs one token
-            rep = rep && n_spilled == sp0 && arrivals_keep(next0, true);
+            // (LAS: members' keys grow past a request that ranks behind the
+            // last of a full batch, which then takes a place in it; see step)
+            rep = rep && pol != P_LAS && n_spilled == sp0 && arrivals_keep(next0, true);
             alone = false;
             if (!rep && free_) plan_join();
         }

@@ -138,3 +138,36 @@ def test_parity_jsq_adaptive_gamma(torch, cfg, R):
     g = gpu_run(w)
     assert_parity(g, o)
     assert np.all(o["switches"][:2] > 0)
+
+
+FULL = SETS + [dict(policy=W.SPF), dict(policy=W.SJF), dict(policy=W.TRAIL), dict(policy=W.LTR),
+               dict(policy=W.BOOST, gamma=1e-3, k=3, memguard=1, delta_us=5000),
+               dict(policy=W.BOOST, gamma=1e-3, ada=dict(W.ADA, window=30, min_samples=20,
+                                                         beta=0.3), **W.VANILLA)]
+
+
+def cluster(arr, P, D, e, R, sets=FULL):
+    return W.Workload("full batches", np.asarray([arr], np.int64), np.asarray([P], np.int32),
+                      np.asarray([D], np.int32), e, np.stack([W.setting(0, **s) for s in sets]),
+                      meta=dict(replicas=R, dispatch="jsq"))
+
+
+def test_jsq_arrival_behind_a_full_batch(torch):
+    """One sequence per replica: a request arrives that ranks behind the only
+    member. Under LAS the member's key grows past it, and it takes the place."""
+    w = cluster([0, 1, 30_000], [10, 10, 30], [100, 300, 5], W.Engine(max_seqs=1), 2)
+    assert_parity(gpu_run(w), oracle.jsq(w, 2))
+
+
+@pytest.mark.parametrize("tokens,kv", [(8192, 16384), (64, 60)])
+@pytest.mark.parametrize("load", [2.0, 4.0])
+@pytest.mark.parametrize("M", [1, 2, 4])
+def test_parity_jsq_full_batches(torch, M, load, tokens, kv):
+    """Batches at the sequence cap, with requests that arrive behind the last
+    member while nothing waits, under every policy; also with the token and
+    the KV budget near their limits."""
+    a, p, d = W.small_random(71 + M, 200, rate_per_s=load * M, p_med=40, d_med=60, p_max=500,
+                             d_max=300)
+    e = W.Engine(max_seqs=M, max_tokens=tokens, chunk=min(tokens, 1024), kv_blocks=kv)
+    w = cluster(a, p, d, e, 2)
+    assert_parity(gpu_run(w), oracle.jsq(w, 2))
