@@ -118,9 +118,9 @@ DEV uint64_t sgpr64(uint64_t x) {
 // A wave-uniform value kept in a vector register: state and constants that a
 // step uses once or twice. Scalar registers are what the simulator runs out
 // of, and a spilled scalar costs a lane write and a lane read where the
-// compiler chooses; there are vector registers to spare at the occupancy the
-// LDS allows. `v` serves lane arithmetic as it is, the conversion gives the
-// scalar.
+// compiler chooses; most builds have vector registers to spare at the
+// occupancy the LDS allows (see sim_kernel). `v` serves lane arithmetic as it
+// is, the conversion gives the scalar.
 template <typename T_>
 struct Held {
     T_ v;
@@ -2615,8 +2615,15 @@ DEV void run_cluster(const SimArgs &a, const DevSetting &st, int inst, unsigned 
 // EXT: the extended build (adaptive gamma, the phase-aware and cache-aware signals,
 // DistBoost, Sarathi), launched when some instance uses one of them (its extra state
 // and code cost the other policies registers). CP: compact list slots. BSH: see Sim.
+// At 64 sequences the LDS holds 16 instances a compute unit, four a SIMD: 128
+// vector registers each. Only the extended four-word build would take one or
+// two more, and is told to stay within them (0: nothing asked). 4,096
+// instances of 1,500 requests, ms a step, 3 and 4 waves: LTR+ on chat 30.8 and
+// 22.7, on reasoning 514 and 507; eight policies mixed on chat 42.2 and 40.0,
+// on reasoning 1,532 and 1,514.
 template <bool EXT, bool CP, int BSH>
-__global__ __launch_bounds__(64) void sim_kernel(SimArgs a) {
+__global__ __launch_bounds__(64)
+__attribute__((amdgpu_waves_per_eu(EXT && !CP ? 4 : 0))) void sim_kernel(SimArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     if ((int)blockIdx.x >= a.n_inst) return;
     const int inst = a.order ? a.order[blockIdx.x] : (int)blockIdx.x;
