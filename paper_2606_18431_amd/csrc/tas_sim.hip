@@ -2204,6 +2204,19 @@ struct Sim {
 
     // ---------------------------------------------------------- driver
 
+    // TRAIL: whether the token budget clips, or could come to clip, the chunk
+    // of the waiting request that closed admissions, the first on the list,
+    // as members that ranked behind it come to rank before it.
+    DEV bool may_clip() const {
+        for (int b = 0; b < L; b += kWave) {
+            const int i = b + lane();
+            const uint4 q = ldq(min(i, L - 1));
+            const uint64_t wm = ballot(i < L && is_waiting(q.x));
+            if (wm) return min(rl(sw(q), ffs0(wm)), (int)c) > T - nb;
+        }
+        return false;
+    }
+
     // Whether a batch that repeats but for the requests that arrived since
     // `next0` still does: those are met after admissions close, or not at
     // all because the batch is full before them, or nothing arrived. Finds
@@ -2217,6 +2230,7 @@ struct Sim {
         uint64_t bar = close_pk;
         if (moved || full) {
             const int at = find_members();
+            if (UNLIKELY(pol == P_TRAIL) && close_pk != ~0ull && may_clip()) return false;
             if (full && at >= 0) {
                 last = at;
                 const uint64_t pk = uniu(S.k[at]);
@@ -2338,10 +2352,14 @@ struct Sim {
         // formation at its last member. Keys that all fall together (SRPT,
         // TRAIL) only take residents from behind a waiting candidate to
         // before it, where they hold the same KV and are no victims, so those
-        // batches repeat too. Sarathi's, which all move to the latest time,
-        // do as long as no resident is left out and no waiting request ranks
-        // before them (it takes no victims by priority). LAS's grow, past
-        // the waiting ones: excluded.
+        // batches repeat too. But they also take a token each there, and the
+        // token budget may then clip the candidate's chunk to one that fits:
+        // under TRAIL, whose protected residents stay behind a candidate that
+        // found no victim (SRPT's do not), its chunk must fit beside the
+        // whole batch (see may_clip). Sarathi's batches, which all move to the
+        // latest time, repeat as long as no resident is left out and no
+        // waiting request ranks before them (it takes no victims by
+        // priority). LAS's keys grow, past the waiting ones: excluded.
         alone = whole && nW == 0 && spill_n == 0;
         bool ok = stays && completed == c0 && pol != P_LAS && n_spilled == sp0 &&
                   (whole || nb == M);

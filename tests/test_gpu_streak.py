@@ -167,3 +167,38 @@ def test_many_completions_at_once(torch, seed, burst, longest):  # noqa: F811
     g = gpu_run(w)
     assert_parity(w, g, o)
     assert_gamma(g, o)
+
+
+@pytest.mark.parametrize("engine", [
+    W.Engine(max_seqs=64, max_tokens=65, chunk=65, kv_blocks=26),
+    W.Engine(max_seqs=64, max_tokens=66, chunk=66, kv_blocks=26),
+    W.Engine(max_seqs=64, max_tokens=67, chunk=66, kv_blocks=26),
+])
+def test_protected_member_passes_a_clipped_prefill(torch, engine):  # noqa: F811
+    """TRAIL: a waiting prefill that takes the whole token budget does not
+    fit; the only resident, which its progress protects, ranks behind it.
+    Once the resident has fewer tokens left it ranks before the prefill and
+    takes a token of the budget: the prefill's chunk shrinks by one, where
+    that crosses a block boundary it fits."""
+    w = edge_workload([0, 1_621_098], [16, 66], [400, 5], engine,
+                      [W.setting(0, W.TRAIL), W.setting(0, W.SRPT), W.setting(0, W.LAS)])
+    o = oracle.run(w)
+    assert_parity(w, gpu_run(w), o)
+
+
+@pytest.mark.parametrize("extended", [False, True], ids=["fixed", "extended"])
+@pytest.mark.parametrize("bs", [1, 16, 24])
+@pytest.mark.parametrize("tokens", [40, 64, 200])
+def test_token_and_kv_budget_bind(torch, tokens, bs, extended):  # noqa: F811
+    """The token budget clips the prefill at which the KV budget closes
+    admissions, all the time, under every policy."""
+    a, p, d = W.small_random(61, 300, rate_per_s=60.0, p_med=90, d_med=60, p_max=700, d_max=400)
+    e = W.Engine(max_seqs=32, max_tokens=tokens, chunk=tokens, block_tokens=bs, max_iters=20_000,
+                 kv_blocks=1200 // bs)
+    sets = POLICIES + LTR if extended else POLICIES[:7]
+    w = edge_workload(a, p, d, e, sets)
+    o = oracle.run(w)
+    assert np.any(o["counters"][:, 3:5] > 0)  # evictions: the KV budget binds
+    g = gpu_run(w)
+    assert np.array_equal(g["status"], o["status"])
+    assert_parity(w, g, o, inst=np.nonzero(o["status"] == 0)[0])
