@@ -183,6 +183,10 @@ DEV int scan_add(int x) {
     return x;
 }
 DEV int wsum(int x) { return rl(scan_add(x), 63); }
+// the same for values from 0 to 2^31 - 1 whose sum may pass them
+DEV int64_t wsum_wide(int x) {
+    return (int64_t)wsum(x & 0xffff) + ((int64_t)wsum(x >> 16) << 16);
+}
 DEV int wmin(int x) {
     x = min(x, dpp<kShr1>(INT32_MAX, x));
     x = min(x, dpp<kShr2>(INT32_MAX, x));
@@ -632,6 +636,13 @@ struct Sim {
         } else {
             return wsum(memb ? blocks(kv + r) - blocks(kv) : 0);
         }
+    }
+
+    // The sum over the wave of each lane's KV tokens of up to 64 requests:
+    // below 2^16 tokens each with compact slots, 2^24 otherwise.
+    DEV int64_t ctx_sum(int x) const {
+        if constexpr (CP) return wsum(x);
+        return wsum_wide(x);
     }
 
     // ---------------------------------------------------------- arrivals
@@ -1498,7 +1509,7 @@ struct Sim {
         if (all_in) U += opened + new_blk;
         maxU = max(maxU.v, U);
         if (nd) {
-            const int kf = wsum(kfree);
+            const int64_t kf = ctx_sum(kfree);
             U -= wsum(ufree);
             sum_ctx -= kf, kv_res -= kf;
             completed += nd;
@@ -1740,7 +1751,7 @@ struct Sim {
         U += grow;
         maxU = max(maxU.v, U);
         if (nd) {
-            const int kf = wsum(kfree);
+            const int64_t kf = ctx_sum(kfree);
             U -= wsum(ufree);
             sum_ctx -= kf, kv_res -= kf;
             completed += nd;

@@ -202,3 +202,20 @@ def test_token_and_kv_budget_bind(torch, tokens, bs, extended):  # noqa: F811
     g = gpu_run(w)
     assert np.array_equal(g["status"], o["status"])
     assert_parity(w, g, o, inst=np.nonzero(o["status"] == 0)[0])
+
+
+@pytest.mark.parametrize("n", [127, 130, 260])
+@pytest.mark.parametrize("D", [1, 3])
+def test_contexts_released_together_past_31_bits(torch, D, n):  # noqa: F811
+    """n requests of nearly 2^24 tokens complete in one iteration (D = 1: at
+    their first token, D = 3: at the end of a run): the context they release
+    passes 2^31, or 2^32. A small one decodes on, at the context's cost."""
+    P = (1 << 24) - 8
+    e = W.Engine(iter_base_us=1000, iter_tok_us=0, iter_ctx_div=1 << 20, max_seqs=n + 1,
+                 chunk=32767, max_tokens=(n + 1) * 32767, kv_blocks=(n + 1) << 20)
+    w = edge_workload(np.zeros(n + 1), [P] * n + [40], [D] * n + [700], e, POLICIES)
+    o = oracle.run(w)
+    assert np.all(o["status"] == 0)
+    assert len(set(o["ttlt"][0][:n])) == 1
+    g = gpu_run(w)
+    assert_parity(w, g, o)
