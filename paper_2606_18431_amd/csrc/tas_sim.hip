@@ -2241,14 +2241,14 @@ struct Sim {
         uint64_t bar = close_pk;
         if (moved || full) {
             const int at = find_members();
-            if (UNLIKELY(pol == P_TRAIL) && close_pk != ~0ull && may_clip()) return false;
             if (full && at >= 0) {
                 last = at;
                 const uint64_t pk = uniu(S.k[at]);
                 bar = sgpr64(pk < bar ? pk : bar);
             }
         }
-        return next == next0 || (bar != ~0ull && !ballot(arr_pk <= bar));
+        if (next != next0 && (bar == ~0ull || ballot(arr_pk <= bar))) return false;
+        return pol != P_TRAIL || close_pk == ~0ull || !may_clip();
     }
 
     // Sarathi: the first live entry of the list is a resident, so no waiting
