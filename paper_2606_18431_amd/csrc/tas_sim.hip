@@ -1198,23 +1198,28 @@ struct Sim {
             const int d = cand ? blocks(kvv + m) - blocks(kvv) : 0;
             const uint64_t cm = ballot(cand), resm = ballot(res);
             int mt = 0, dt = 0;  // tokens and blocks of the lanes admitted
-            bool all = closed || !tight;
-            if (all) {  // do all candidates fit?
+            int path = 1;  // 0: all fit, 1: count lanes, 2: prefix sums
+            if (closed || !tight) {  // do all candidates fit?
                 const uint64_t big = ballot(m > 1);
-                mt = popc(cm), dt = popc(ballot(d > 0));
-                if (big & (big - 1)) {
-                    mt = wsum(m), dt = wsum(d);
-                } else if (big) {
-                    const int l = ffs0(big), db = rl(d, l);
-                    mt += rl(m, l) - 1;
-                    dt += db > 0 ? db - 1 : 0;
+                if (UNLIKELY((big & (big - 1)) != 0)) {
+                    // several long chunks: their totals take the sums anyway
+                    // (LAS under KV pressure, where most formations have
+                    // such: 3 to 6 % of a step against summing twice)
+                    path = 2;
+                } else {
+                    mt = popc(cm), dt = popc(ballot(d > 0));
+                    if (big) {
+                        const int l = ffs0(big), db = rl(d, l);
+                        mt += rl(m, l) - 1;
+                        dt += db > 0 ? db - 1 : 0;
+                    }
+                    path = cnt + popc(cm) <= M && mt <= T - used && dt <= Kb - U ? 0 : 1;
                 }
-                all = cnt + popc(cm) <= M && mt <= T - used && dt <= Kb - U;
             }
             uint64_t okm = cm, bad = 0;
             int n = m, du = d;
-            bool scan = !all;
-            if (scan) {
+            bool scan = path != 0;
+            if (path == 1) {
                 // Up to the first candidate that computes more than a token,
                 // counting lanes gives the prefix sums (two chains of six
                 // dependent lane moves). Where the KV budget binds, the
