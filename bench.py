@@ -133,8 +133,8 @@ def main():
     ap.add_argument("--list-cap", type=int, default=0,
                     help="on-chip candidate list per instance (0: the library default)")
     ap.add_argument("--check", action="store_true",
-                    help="run the checking build (libtas_check.so): every instance's state is "
-                         "verified after each iteration")
+                    help="run the checking build (libtas_check.so): every batch, run of repeated "
+                         "iterations and instance state is verified")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="only run a plain 1 GiB device-to-device copy (the reference for "
                          "scaling rocprofv3 FETCH_SIZE / WRITE_SIZE)")

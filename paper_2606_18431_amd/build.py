@@ -1,6 +1,6 @@
 """Build the HIP libraries for gfx950 with hipcc, in-tree: libtas.so, and
-libtas_check.so, the same entry points with every instance's state verified
-after each iteration (TAS_CHECK_INVARIANTS)."""
+libtas_check.so, the same entry points with every batch, every run of
+repeated iterations and every instance's state verified (TAS_CHECK_INVARIANTS)."""
 from __future__ import annotations
 
 import os

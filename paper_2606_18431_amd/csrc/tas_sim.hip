@@ -41,9 +41,11 @@ namespace {
 #define DEV __device__ __forceinline__
 
 // The checking build (a library of its own, compiled with
-// TAS_CHECK_INVARIANTS=1) verifies the state of every instance after each
-// iteration and fails the instance with S_ESTATE at the first violation;
-// its results are otherwise those of the ordinary build.
+// TAS_CHECK_INVARIANTS=1) verifies the batch of every iteration that is
+// formed, the members of every run of repeated iterations before it is
+// applied, and the state of every instance after each step (an iteration, or
+// the runs up to the next event). It fails the instance with S_ESTATE at the
+// first violation; its results are otherwise those of the ordinary build.
 #ifndef TAS_CHECK_INVARIANTS
 #define TAS_CHECK_INVARIANTS 0
 #endif
@@ -1617,6 +1619,10 @@ struct Sim {
                 if (r == 0) return 0;
             }
         }
+        if constexpr (kCheck) {
+            check_run(r);
+            if (status) return 0;
+        }
         // apply r iterations (counted before the loop: a sum the compiler also finds
         // in a lane's branch would make the count lane-dependent)
         const int64_t it_end = (int64_t)sgpr64((uint64_t)(iters + r));
@@ -2147,11 +2153,51 @@ struct Sim {
 
     // The batch just formed respects the sequence cap, the token budget and
     // the KV budget, and every member computes at least one token.
+    // Before a run of r repeated iterations is applied: its members are the
+    // first nb residents, all within the chunks that the run visits, each
+    // needs one token at a time and has r left; the batch respects its caps
+    // and the blocks it grows by the KV budget; and, with adaptive gamma,
+    // those that complete stand in the order of the keys that the r-th
+    // iteration starts with.
+    DEV void check_run(int r) {
+        bool bad = r < 1 || r > kWave || nb < 1 || nb > M || nb > T;
+        int n = 0, grow = 0;
+        uint64_t top = 0;  // 1 + the largest key of those that complete so far (0: none)
+        for (int b = 0; b < L && !bad; b += kWave) {
+            const int i = b + lane();
+            const uint4 q = ldq(min(i, L - 1));
+            const uint32_t g = i < L ? q.x : 0u;
+            const bool memb = (g & G_RES) != 0 && i <= last;
+            const int w = sw(q), kv = skv(q), left = sleft(q);
+            n += popc(ballot(memb));
+            grow += growth(memb, kv, r);
+            bad = bad || ballot(memb && (kv + 1 != w || left < r || (g & (G_INB | G_EVI)))) != 0;
+            bad = bad || (ballot(memb) && !((emit_chunks >> (b >> 6)) & 1ull));
+            if constexpr (EXT) {
+                if (ad) {
+                    const uint64_t pk = S.k[min(i, L - 1)];
+                    const int ix = min(idx_of(pk), N.v - 1);
+                    int sig = w + r - 1;
+                    if (phase_signal) sig -= Pp()[ix];
+                    if (cache_signal) sig -= Hp()[ix];
+                    const int ol = (int)((g >> G_LVL_SHIFT) & 31u), nl = level_of(sig, k.v, lk.v);
+                    const uint64_t at = pack(key_of(pk) + S.bt[ol] - S.bt[nl], ix);
+                    for (uint64_t m = ballot(memb && left == r); m; m &= m - 1) {
+                        const uint64_t x = rlu(at, ffs0(m)) + 1;
+                        bad = bad || x <= top;
+                        top = x;
+                    }
+                }
+            }
+        }
+        if (bad || n != nb || grow > Kb - U) fail(S_ESTATE);
+    }
+
     DEV void check_batch() {
         if (cnt < 1 || cnt > M || used < cnt || used > T || U < 0 || U > Kb) fail(S_ESTATE);
     }
 
-    // The state between iterations: the list's residents, waiting entries
+    // The state between steps: the list's residents, waiting entries
     // and holes match their counts; the KV in use is the residents' blocks,
     // within the budget, and their tokens the running sum; the keys of the entries other than holes ascend
     // strictly; holes lie at or after lo_hole; no mark of an iteration (in
@@ -2303,6 +2349,9 @@ struct Sim {
             // nothing waits or arrived: straight on, the order can wait
             if (!alone || due || nR == 0 || n_holes >= kHoleLimit) break;
             nb = nR;
+        }
+        if constexpr (kCheck) {
+            if (status) return;
         }
         if (run) {
             lo_mod = lo_pend, nmoved = nm_pend;

@@ -19,8 +19,9 @@ from . import workloads as W
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(PKG, "libtas.so")
-# the checking build: the same entry points, and every instance's state is
-# verified after each iteration (a violation fails it with TAS_ESTATE)
+# the checking build: the same entry points, and every batch, every run of
+# repeated iterations and every instance's state after each step is verified
+# (a violation fails the instance with TAS_ESTATE)
 CHECK_LIB_PATH = os.path.join(PKG, "libtas_check.so")
 LEVELS = 24
 

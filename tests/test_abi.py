@@ -33,8 +33,8 @@ def test_library_exports_every_declared_symbol():
 
 
 def test_checking_build_exports_the_same_symbols():
-    """libtas_check.so (every instance's state verified after each
-    iteration) is a drop-in replacement: the same entry points."""
+    """libtas_check.so (every batch, run and instance state verified) is a
+    drop-in replacement: the same entry points."""
     assert os.path.exists(tas.CHECK_LIB_PATH), "libtas_check.so is missing: run the build"
     lib = ctypes.CDLL(tas.CHECK_LIB_PATH)
     for n in declared_functions():

@@ -1,8 +1,12 @@
 """The checking build (libtas_check.so) on the GPU.
 
-It runs the same kernels as libtas.so and, after every simulated iteration
-of every instance, verifies the state: the batch respects the sequence cap,
-the token budget and the KV budget; the list's residents, waiting entries
+It runs the same kernels as libtas.so and verifies every batch that is
+formed (it respects the sequence cap, the token budget and the KV budget),
+every run of repeated iterations before it is applied (its members are the
+residents that lead the list, each needs one token at a time and has that
+many left, the blocks fit, and those that complete stand in key order where
+gamma adapts) and the state of every instance after each step, that is an
+iteration or the runs up to the next event: the list's residents, waiting entries
 and holes match their counts; the KV in use is the residents' blocks; the
 keys of the live entries ascend strictly; no mark of an iteration survives
 it; every spilled entry is waiting and the spill's minimum is exact; every
@@ -11,7 +15,9 @@ with TAS_ESTATE. Each workload below must finish with no violation and with
 the ordinary build's outputs, byte for byte. The workloads cover the spill
 and refill paths (the smallest lists), the retry pass, evictions under KV
 pressure, every comparator, adaptive gamma, the phase ladder, the
-cache-aware signal and the JSQ router; and every full-size workload with
+cache-aware signal and the JSQ router; the edges of runs (completions in one
+iteration beside level crossings, batches at their caps); and every full-size
+workload with
 stored oracle digests (configs 1-3, the large sweep and its other settings
 grids, the starvation mix), checked against those digests.
 """
@@ -21,6 +27,8 @@ import numpy as np
 import pytest
 
 from paper_2606_18431_amd import workloads as W
+from test_gpu_jsq import full_batches
+from test_gpu_streak import LTR, POLICIES, bursts, crossing_before_completions, tight_budgets
 
 pytestmark = pytest.mark.gpu
 
@@ -86,12 +94,21 @@ def case(name):
         return residents_burst_workload(), dict(list_cap=72)
     if name == "large-sweep-law":
         return W.make(4, n_traces=1, n_settings=16, n_req=20000), {}
+    if name == "crossing-before-completions":
+        return crossing_before_completions(65), {}
+    if name == "completions-at-once":
+        return bursts(24, 25, 200), {}
+    if name == "tight-budgets":
+        return tight_budgets(64, 16, POLICIES + LTR), {}
+    if name == "jsq-full-batches":
+        return full_batches(2, 2.0, 64, 60), {}
     raise KeyError(name)
 
 
 CASES = ["config0", "kv-pressure-minimum-list", "bursty-spill", "comparators-spill",
          "adaptive-gamma-spill", "ladder-spill", "cache-spill", "jsq", "residents-retry",
-         "large-sweep-law"]
+         "large-sweep-law", "crossing-before-completions", "completions-at-once",
+         "tight-budgets", "jsq-full-batches"]
 
 
 def run_with(path, w, kw):

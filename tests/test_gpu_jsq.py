@@ -159,6 +159,13 @@ def test_jsq_arrival_behind_a_full_batch(torch):
     assert_parity(gpu_run(w), oracle.jsq(w, 2))
 
 
+def full_batches(M, load, tokens, kv):
+    a, p, d = W.small_random(71 + M, 200, rate_per_s=load * M, p_med=40, d_med=60, p_max=500,
+                             d_max=300)
+    e = W.Engine(max_seqs=M, max_tokens=tokens, chunk=min(tokens, 1024), kv_blocks=kv)
+    return cluster(a, p, d, e, 2)
+
+
 @pytest.mark.parametrize("tokens,kv", [(8192, 16384), (64, 60)])
 @pytest.mark.parametrize("load", [2.0, 4.0])
 @pytest.mark.parametrize("M", [1, 2, 4])
@@ -166,8 +173,5 @@ def test_parity_jsq_full_batches(torch, M, load, tokens, kv):
     """Batches at the sequence cap, with requests that arrive behind the last
     member while nothing waits, under every policy; also with the token and
     the KV budget near their limits."""
-    a, p, d = W.small_random(71 + M, 200, rate_per_s=load * M, p_med=40, d_med=60, p_max=500,
-                             d_max=300)
-    e = W.Engine(max_seqs=M, max_tokens=tokens, chunk=min(tokens, 1024), kv_blocks=kv)
-    w = cluster(a, p, d, e, 2)
+    w = full_batches(M, load, tokens, kv)
     assert_parity(gpu_run(w), oracle.jsq(w, 2))

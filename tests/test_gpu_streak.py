@@ -121,13 +121,9 @@ def assert_gamma(g, o):
     assert np.array_equal(g["switches"], o["switches"])
 
 
-@pytest.mark.parametrize("ahead", [0, 1, 2, 20, 63, 64, 65, 130])
-def test_two_completions_after_a_crossing(torch, ahead):  # noqa: F811
+def crossing_before_completions(ahead):
     """Two requests complete in one iteration; the older one crossed a level
-    `ahead` iterations before, which moved it behind the other in the batch.
-    Their latencies enter gamma's window in batch order, and a window that is
-    full later drops the one that entered first: with 21 latencies the
-    largest or the second largest, so that gamma differs by the order."""
+    `ahead` iterations before, which moved it behind the other in the batch."""
     e = W.Engine(iter_ctx_div=1_000_000, iter_tok_us=0)  # 5 ms an iteration
     DA, later = 200, 20
     arr, P, D = [0, later * 5000], [512 - (DA - ahead), 100], [DA, DA - later]
@@ -136,9 +132,17 @@ def test_two_completions_after_a_crossing(torch, ahead):  # noqa: F811
         P.append(16)
         D.append(90 if i == 20 else 2 + i % 3)
     ada = dict(W.ADA, window=21, min_samples=20, beta=0.3)
-    w = edge_workload(arr, P, D, e,
-                      [W.setting(0, W.BOOST, gamma=1e-3, ada=dict(ada, window=n), **W.UNIBOOST)
-                       for n in (20, 21, 22)])
+    return edge_workload(arr, P, D, e,
+                         [W.setting(0, W.BOOST, gamma=1e-3, ada=dict(ada, window=n), **W.UNIBOOST)
+                          for n in (20, 21, 22)])
+
+
+@pytest.mark.parametrize("ahead", [0, 1, 2, 20, 63, 64, 65, 130])
+def test_two_completions_after_a_crossing(torch, ahead):  # noqa: F811
+    """Their latencies enter gamma's window in batch order, and a window that
+    is full later drops the one that entered first: with 21 latencies the
+    largest or the second largest, so that gamma differs by the order."""
+    w = crossing_before_completions(ahead)
     o = oracle.run(w)
     done = w.arrival_us[0] + o["ttlt"]
     assert np.all(done[:, 0] == done[:, 1])
@@ -147,11 +151,9 @@ def test_two_completions_after_a_crossing(torch, ahead):  # noqa: F811
     assert_gamma(g, o)
 
 
-@pytest.mark.parametrize("seed,burst,longest", [(24, 25, 200), (12, 10, 600), (6, 50, 100)])
-def test_many_completions_at_once(torch, seed, burst, longest):  # noqa: F811
+def bursts(seed, burst, longest):
     """Bursts of requests that arrive apart and complete together, on every
-    80th iteration, after level crossings in quiet stretches: several
-    latencies enter small windows at once, all the time."""
+    80th iteration, after level crossings in quiet stretches."""
     rng = np.random.default_rng(seed)
     n = 500
     m = np.sort(np.concatenate([400 * b + rng.integers(0, 60, burst) for b in range(n // burst)]))
@@ -161,7 +163,13 @@ def test_many_completions_at_once(torch, seed, burst, longest):  # noqa: F811
                       **kw)
             for g0 in (1e-4, 1e-2) for k, b in ((21, 0.05), (33, 0.3), (100, 1.0))
             for kw in (W.UNIBOOST, W.VANILLA, dict(k=7, signal=1))]
-    w = edge_workload(m * 5000, rng.integers(1, longest, n), D, e, sets)
+    return edge_workload(m * 5000, rng.integers(1, longest, n), D, e, sets)
+
+
+@pytest.mark.parametrize("seed,burst,longest", [(24, 25, 200), (12, 10, 600), (6, 50, 100)])
+def test_many_completions_at_once(torch, seed, burst, longest):  # noqa: F811
+    """Several latencies enter small windows at once, all the time."""
+    w = bursts(seed, burst, longest)
     o = oracle.run(w)
     assert np.all(o["status"] == 0) and np.all(o["switches"] > 0)
     g = gpu_run(w)
@@ -186,17 +194,20 @@ def test_protected_member_passes_a_clipped_prefill(torch, engine):  # noqa: F811
     assert_parity(w, gpu_run(w), o)
 
 
+def tight_budgets(tokens, bs, sets):
+    """The token budget clips the prefill at which the KV budget closes
+    admissions, all the time."""
+    a, p, d = W.small_random(61, 300, rate_per_s=60.0, p_med=90, d_med=60, p_max=700, d_max=400)
+    e = W.Engine(max_seqs=32, max_tokens=tokens, chunk=tokens, block_tokens=bs, max_iters=20_000,
+                 kv_blocks=1200 // bs)
+    return edge_workload(a, p, d, e, sets)
+
+
 @pytest.mark.parametrize("extended", [False, True], ids=["fixed", "extended"])
 @pytest.mark.parametrize("bs", [1, 16, 24])
 @pytest.mark.parametrize("tokens", [40, 64, 200])
 def test_token_and_kv_budget_bind(torch, tokens, bs, extended):  # noqa: F811
-    """The token budget clips the prefill at which the KV budget closes
-    admissions, all the time, under every policy."""
-    a, p, d = W.small_random(61, 300, rate_per_s=60.0, p_med=90, d_med=60, p_max=700, d_max=400)
-    e = W.Engine(max_seqs=32, max_tokens=tokens, chunk=tokens, block_tokens=bs, max_iters=20_000,
-                 kv_blocks=1200 // bs)
-    sets = POLICIES + LTR if extended else POLICIES[:7]
-    w = edge_workload(a, p, d, e, sets)
+    w = tight_budgets(tokens, bs, POLICIES + LTR if extended else POLICIES[:7])
     o = oracle.run(w)
     assert np.any(o["counters"][:, 3:5] > 0)  # evictions: the KV budget binds
     g = gpu_run(w)
